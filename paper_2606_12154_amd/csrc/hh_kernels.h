@@ -49,6 +49,9 @@ void finalize(hipStream_t st, int r0, int n, const int* row_stream, const int* r
 // dst[0 .. n) = src[0 .. n) (host ints) through kernel arguments, kPutInts per launch.
 constexpr int kPutInts = 62;
 void put_ints(hipStream_t st, int* dst, const int* src, int n);
+// Position, pending token and argmax slot of streams [s0, s0 + n) to zero,
+// and the decode-step error word (when given).
+void reset_streams(hipStream_t st, int s0, int n, int* pos, int* pending, unsigned long long* slot, int* err);
 
 // fp32 scratch (in the context's arena) for split-K partial tiles of the
 // MFMA GEMM; splits are reduced until the partials fit.
@@ -104,8 +107,10 @@ struct GemmKernels {
                     const float* gain = nullptr, float eps = 0.f, TM* h = nullptr, const TM* Wt = nullptr,
                     float* ss = nullptr, int* cnt = nullptr, int ncnt = 0);
   static bool norm_fusable(int N);
-  // h = rmsnorm(x) * gain, one row per workgroup (norm_fusable(N)).
-  static void rmsnorm(hipStream_t st, int M, float* x, int N, const float* gain, float eps, TM* h);
+  // h = rmsnorm(x) * gain, one row per workgroup (norm_fusable(N)); with
+  // rows, h's row i comes from x's row rows[i].
+  static void rmsnorm(hipStream_t st, int M, float* x, int N, const float* gain, float eps, TM* h,
+                      const int* rows = nullptr);
   static void gateup(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int F, float scale, TM* m,
                      const TM* Wt = nullptr, const RowNorm& rn = RowNorm());
   static void logits(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int V, float scale, float* logits,
@@ -119,6 +124,16 @@ struct GemmKernels {
 bool flash_prefill_supported(int G, int max_context, size_t layer_kv_elems);
 void flash_prefill(hipStream_t st, const _Float16* qM, const _Float16* kv, KvLayout L, int layer,
                    const int* page_table, int s, int p0, int n_rows, int hq, int hkv, _Float16* oM);
+// The same for a pass that holds rows of several streams, each stream's rows
+// consecutive: one item per pair of 32-query blocks (pair < ceil(blocks / 2))
+// of each stream's rows.  q: rotated fp32 queries of every row of the pass.
+struct FlashItem {
+  int stream, pos;  // the stream, and the position of its first row in the pass
+  int row, rows;    // that row's index in the pass, and how many rows follow
+  int pair;
+};
+void flash_prefill_packed(hipStream_t st, const float* q, const _Float16* kv, KvLayout L, int layer,
+                          const int* page_table, const FlashItem* items, int n_items, int hq, int hkv, _Float16* oM);
 
 // ---- batch-1 decode step as one persistent kernel (k_step.hip)
 constexpr int kStepThreads = 512;     // threads per workgroup (8 waves)

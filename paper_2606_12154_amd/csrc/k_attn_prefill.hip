@@ -74,12 +74,30 @@ struct FlashCfg {
   static_assert(LDS <= 160 * 1024, "LDS");
 };
 
-template <int G, int NS>
+// PACK: the pass holds rows of several streams; workgroup blockIdx.x takes the
+// query-block pair of items[blockIdx.x] instead of pair blockIdx.x of one
+// stream's rows.  Its queries come as fp32 and enter the products as fp16
+// high and low parts, and so do the softmax weights: such rows were attended
+// in fp32 (the row kernel of lockstep decoding, one workgroup per row and kv
+// head), and two terms of 11 bits keep that precision.
+template <int G, int NS, bool PACK>
 __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* __restrict__ qM,
+                                                               const float* __restrict__ q32,
                                                                const _Float16* __restrict__ kv, KvLayout L, int layer,
-                                                               const int* __restrict__ page_table, int s, int p0,
+                                                               const int* __restrict__ page_table,
+                                                               const FlashItem* __restrict__ items, int s, int p0,
                                                                int n_rows, int hq, _Float16* __restrict__ oM) {
   using C = FlashCfg<G, NS>;
+  int p = blockIdx.x;
+  if constexpr (PACK) {
+    const FlashItem it = items[blockIdx.x];
+    s = it.stream;
+    p0 = it.pos;
+    n_rows = it.rows;
+    p = it.pair;
+    q32 += (size_t)it.row * hq * 64;
+    oM += (size_t)it.row * hq * 64;
+  }
   extern __shared__ __attribute__((aligned(16))) char smem[];
   int* pt = reinterpret_cast<int*>(smem + (C::LDS - C::PT));  // physical pages of keys 0 .. kend-1
   // Causal work is balanced by pairing query blocks: workgroup (p, g, hh)
@@ -92,7 +110,6 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
   constexpr int GH = G / 2;  // query heads per workgroup
   const int g = blockIdx.y, hh = blockIdx.z;
   const int nqb = (n_rows + 31) / 32;
-  const int p = blockIdx.x;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hi = wave % G, grp = wave / G;
   const int qsel = ((hi / GH) + grp) & 1;                  // 0: block p, 1: block nqb - 1 - p
@@ -113,11 +130,24 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
   const int qpos = p0 + qrow;
   const float scale = 0.125f * 1.4426950408889634f;  // 1/sqrt(64) * log2(e)
 
-  f16x8 qf[4];
+  f16x8 qf[4], ql[PACK ? 4 : 1];  // ql: low parts
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) {
-    if (qvalid) qf[ks] = *reinterpret_cast<const f16x8*>(qM + ((size_t)qrow * hq + j) * 64 + 16 * ks + 8 * h);
-    else qf[ks] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    qf[ks] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+    if constexpr (PACK) {
+      ql[ks] = qf[ks];
+      if (qvalid) {
+        const f32x4* src = reinterpret_cast<const f32x4*>(q32 + ((size_t)qrow * hq + j) * 64 + 16 * ks + 8 * h);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float v = src[e >> 2][e & 3];
+          qf[ks][e] = (_Float16)v;
+          ql[ks][e] = (_Float16)(v - (float)qf[ks][e]);
+        }
+      }
+    } else if (qvalid) {
+      qf[ks] = *reinterpret_cast<const f16x8*>(qM + ((size_t)qrow * hq + j) * 64 + 16 * ks + 8 * h);
+    }
   }
   float m = -INFINITY, lsum = 0.f;
   f32x16 o0, o1;
@@ -186,6 +216,7 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
     for (int ks = 0; ks < 4; ++ks) {
       const f16x8 kf = *reinterpret_cast<const f16x8*>(kbuf + c * C::KT_LD + 16 * ks + 8 * h);
       sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf[ks], sacc, 0, 0, 0);
+      if constexpr (PACK) sacc = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, ql[ks], sacc, 0, 0, 0);
     }
 
     // The softmax is the VALU side of the loop (four waves per SIMD share it
@@ -218,12 +249,13 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
     // below the normal range flush to zero, which a softmax weight can take).
     const float alpha = __builtin_amdgcn_exp2f(m - mref);
     float ls = 0.f;
-    f16x8 pb[2];
+    f16x8 pb[2], pl[PACK ? 2 : 1];  // pl: low parts
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[i], scale, -mref));
       ls += pv;
       pb[i >> 3][i & 7] = (_Float16)pv;
+      if constexpr (PACK) pl[i >> 3][i & 7] = (_Float16)(pv - (float)pb[i >> 3][i & 7]);
     }
     lsum = lsum * alpha + ls;
     if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
@@ -248,6 +280,10 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
       }
       o0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, pb[t2], o0, 0, 0, 0);
       o1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, pb[t2], o1, 0, 0, 0);
+      if constexpr (PACK) {
+        o0 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, pl[t2], o0, 0, 0, 0);
+        o1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, pl[t2], o1, 0, 0, 0);
+      }
     }
     m = mn;
   };
@@ -334,17 +370,19 @@ bool flash_prefill_supported(int G, int max_context, size_t layer_kv_elems) {
          layer_kv_elems <= 0xFFFFFFFFull;
 }
 
-template <int G, int NS>
-static void launch_flash(hipStream_t st, dim3 grid, const _Float16* qM, const _Float16* kv, KvLayout L, int layer,
-                         const int* page_table, int s, int p0, int n_rows, int hq, _Float16* oM) {
+template <int G, int NS, bool PACK>
+static void launch_flash(hipStream_t st, dim3 grid, const _Float16* qM, const float* q32, const _Float16* kv,
+                         KvLayout L, int layer, const int* page_table, const FlashItem* items, int s, int p0,
+                         int n_rows, int hq, _Float16* oM) {
   using C = FlashCfg<G, NS>;
   static bool attr = false;
   if (!attr) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_flash_prefill<G, NS>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_flash_prefill<G, NS, PACK>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     attr = true;
   }
-  k_flash_prefill<G, NS><<<grid, C::THREADS, C::LDS, st>>>(qM, kv, L, layer, page_table, s, p0, n_rows, hq, oM);
+  k_flash_prefill<G, NS, PACK><<<grid, C::THREADS, C::LDS, st>>>(qM, q32, kv, L, layer, page_table, items, s, p0,
+                                                                 n_rows, hq, oM);
 }
 
 void flash_prefill(hipStream_t st, const _Float16* qM, const _Float16* kv, KvLayout L, int layer,
@@ -352,10 +390,28 @@ void flash_prefill(hipStream_t st, const _Float16* qM, const _Float16* kv, KvLay
   const int G = hq / hkv;
   // Pairs of query blocks x kv heads x two halves of each kv head's query heads.
   dim3 grid(((n_rows + 31) / 32 + 1) / 2, hkv, 2);
-  switch (G) {
-    case 4: launch_flash<4, 4>(st, grid, qM, kv, L, layer, page_table, s, p0, n_rows, hq, oM); break;
-    default: launch_flash<8, 2>(st, grid, qM, kv, L, layer, page_table, s, p0, n_rows, hq, oM); break;
-  }
+  if (G == 4)
+    launch_flash<4, 4, false>(st, grid, qM, nullptr, kv, L, layer, page_table, nullptr, s, p0, n_rows, hq, oM);
+  else
+    launch_flash<8, 2, false>(st, grid, qM, nullptr, kv, L, layer, page_table, nullptr, s, p0, n_rows, hq, oM);
+}
+
+// One key-split group (256 threads, three workgroups a CU) once the launch has
+// three workgroups per CU, two below: fewer, longer chains while the chip is
+// full, shorter ones while it is not.  Measured per layer, one / two / four
+// groups: 32 prompts of about 99 rows (1,056 workgroups) 31 / 39 / 67 us, 32 of
+// 256 (2,048) 78 / 95 / 148 us; a prefill call of 8 x 64 rows after 512
+// positions (128 workgroups) 3.11 / 2.89 / 3.02 ms, of 2 x 64 rows after 8,000
+// 5.91 / 4.08 / 4.38 ms.
+void flash_prefill_packed(hipStream_t st, const float* q, const _Float16* kv, KvLayout L, int layer,
+                          const int* page_table, const FlashItem* items, int n_items, int hq, int hkv, _Float16* oM) {
+  const dim3 grid(n_items, hkv, 2);
+  if (hq / hkv == 8)
+    launch_flash<8, 1, true>(st, grid, nullptr, q, kv, L, layer, page_table, items, 0, 0, 0, hq, oM);
+  else if ((long long)n_items * hkv * 2 >= 3 * 256)
+    launch_flash<4, 1, true>(st, grid, nullptr, q, kv, L, layer, page_table, items, 0, 0, 0, hq, oM);
+  else
+    launch_flash<4, 2, true>(st, grid, nullptr, q, kv, L, layer, page_table, items, 0, 0, 0, hq, oM);
 }
 
 }  // namespace hh

@@ -900,6 +900,21 @@ void put_ints(hipStream_t st, int* dst, const int* src, int n) {
   }
 }
 
+__global__ void k_reset_streams(int s0, int n, int* __restrict__ pos, int* __restrict__ pending,
+                                unsigned long long* __restrict__ slot, int* __restrict__ err) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) {
+    pos[s0 + i] = 0;
+    pending[s0 + i] = 0;
+    slot[s0 + i] = 0ull;
+  }
+  if (i == 0 && err) *err = 0;
+}
+
+void reset_streams(hipStream_t st, int s0, int n, int* pos, int* pending, unsigned long long* slot, int* err) {
+  k_reset_streams<<<(n + 63) / 64, 64, 0, st>>>(s0, n, pos, pending, slot, err);
+}
+
 void finalize(hipStream_t st, int r0, int n, const int* row_stream, const int* row_pos, unsigned long long* slot,
               int* pending, int* hist, int* pos, int max_ctx) {
   k_finalize<<<1, 64, 0, st>>>(r0, n, row_stream, row_pos, slot, pending, hist, pos, max_ctx);

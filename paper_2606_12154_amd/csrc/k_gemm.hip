@@ -1414,10 +1414,10 @@ constexpr int kNormSplitBatch = 8;  // split partials in flight per chunk
 template <typename TM>
 __global__ __launch_bounds__(256) void k_resid_norm(const float* __restrict__ partial, int splits, int M, int N, float scale,
                                                     float* __restrict__ x, const float* __restrict__ gain, float eps,
-                                                    TM* __restrict__ h) {
+                                                    TM* __restrict__ h, const int* __restrict__ rows) {
   __shared__ float red[4];
   const int row = blockIdx.x, nc = N >> 2;
-  float4* xr = reinterpret_cast<float4*>(x + (size_t)row * N);
+  float4* xr = reinterpret_cast<float4*>(x + (size_t)(rows ? rows[row] : row) * N);
   float4 v[kNormMaxChunks], g[kNormMaxChunks];
   // The gains load with the row, so the second half waits on no global load.
 #pragma unroll
@@ -1520,13 +1520,14 @@ bool GemmKernels<TM, TKV>::resid(hipStream_t st, GemmWorkspace ws, const TM* A, 
   }
   int fused = 0;
   const int sp = run_gemm<TM>(st, ws, A, M, W, K, N, e, GemmKind::Resid, norm, Wt, rn, &fused);
-  if (norm && !fused) k_resid_norm<TM><<<M, 256, 0, st>>>(ws.ptr, sp > 1 ? sp : 0, M, N, scale, x, gain, eps, h);
+  if (norm && !fused) k_resid_norm<TM><<<M, 256, 0, st>>>(ws.ptr, sp > 1 ? sp : 0, M, N, scale, x, gain, eps, h, nullptr);
   return fused != 0;
 }
 
 template <typename TM, typename TKV>
-void GemmKernels<TM, TKV>::rmsnorm(hipStream_t st, int M, float* x, int N, const float* gain, float eps, TM* h) {
-  k_resid_norm<TM><<<M, 256, 0, st>>>(nullptr, 0, M, N, 1.f, x, gain, eps, h);
+void GemmKernels<TM, TKV>::rmsnorm(hipStream_t st, int M, float* x, int N, const float* gain, float eps, TM* h,
+                                   const int* rows) {
+  k_resid_norm<TM><<<M, 256, 0, st>>>(nullptr, 0, M, N, 1.f, x, gain, eps, h, rows);
 }
 
 template <typename TM, typename TKV>

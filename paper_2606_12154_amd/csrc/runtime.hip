@@ -46,7 +46,7 @@ struct Layout {
   std::vector<size_t> wqkvQ, woQ, wguQ, wdownTQ;
   size_t lm_headQ;
   size_t final_norm, rope, kv, page_table, pos, pending, slot, hist, ll, ll_words, layer_tab, trace;
-  size_t row_stream, row_pos, feed, x, h, q, qM, o32, oM, m32, mM, part, logits, gemm_ws, gemm_ws_bytes, scratch_u32;
+  size_t row_stream, row_pos, feed, items, x, h, q, qM, o32, oM, m32, mM, part, logits, gemm_ws, gemm_ws_bytes, scratch_u32;
   // RowNorm buffers of the lockstep decode rows: column-block counters (zero
   // between launches; in the zero-initialised range) and row sums of squares.
   size_t nrm_cnt, nrm_ss;
@@ -192,6 +192,9 @@ Layout make_layout(const hh_config& c) {
   L.row_stream = take(R * 4);
   L.row_pos = take(R * 4);
   L.feed = take(R * 4);
+  // Query-block pairs of a multi-stream prefill pass: at most one per 64 rows
+  // and one more per stream.
+  L.items = take((R / 64 + c.max_streams) * sizeof(FlashItem));
   L.x = take(R * d * 4);
   L.h = take(R * std::max(d, (size_t)hq * 64) * tm);
   L.q = take(R * hq * 64 * 4);
@@ -279,10 +282,11 @@ KvLayout kv_layout(const hh_ctx* c) { return KvLayout{c->L.n_pages, c->cfg.n_kv_
 // streaming path; otherwise the MFMA GEMM path.  s_max: attention splits
 // (1 = direct output).  head_row >= 0: LM head + argmax of that row only;
 // head_row == -1: LM head + argmax of every row (multi-stream decode);
-// head_row == -2: no head.
+// head_row == -2: no head.  n_items > 0: a multi-stream prefill pass whose
+// query-block pairs are in L.items.
 template <typename TW, typename TKV, typename TM>
 void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row, float* logits,
-                    int prefill_stream = -1, int prefill_pos = 0) {
+                    int prefill_stream = -1, int prefill_pos = 0, int n_items = 0) {
   using DK = DecodeKernels<TW, TKV, TM>;
   using GK = GemmKernels<TM, TKV>;
   const hh_config& g = c->cfg;
@@ -359,6 +363,10 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
                         kl, l, pt, prefill_stream, prefill_pos, n, hq, hkv, reinterpret_cast<_Float16*>(oM));
       } else if (prefill_stream >= 0) {
         DK::attention(st, n, q, kv, kl, l, pt, rs, rp, hq, hkv, 1, c->at<float>(L.part), o32, oM);
+      } else if (n_items > 0) {
+        if constexpr (sizeof(TKV) == 2)
+          flash_prefill_packed(st, q, reinterpret_cast<const _Float16*>(kv), kl, l, pt, c->at<FlashItem>(L.items),
+                               n_items, hq, hkv, reinterpret_cast<_Float16*>(oM));
       } else {
         DK::attention_rows(st, n, q, kv, kl, l, pt, rs, rp, hq, hkv, o32, oM, qf);
       }
@@ -676,23 +684,50 @@ hh_status do_prefill_batch(hh_ctx* c, int n, const int32_t* ids, const int32_t* 
       }
     }
     const int R = (int)rs.size(), ne = (int)last_r.size();
+    // fp16 caches: MFMA attention over each stream's rows once the row kernel
+    // would have 1.5 workgroups per CU (32 prompts of about 99 rows: 720 ->
+    // 31 us a layer, 32 of 256: 2,100 -> 78 us).  Its chain over a stream's
+    // keys is longer, so few rows on long contexts stay with the row kernel
+    // (whole calls, row kernel / MFMA: 2 x 8 rows after 2,000 positions 1.35 /
+    // 1.55 ms, after 8,000 2.41 / 3.04 ms; 8 x 8 after 2,000 2.18 / 1.93 ms;
+    // 2 x 64 after 8,000 7.36 / 4.08 ms).
+    std::vector<FlashItem> items;
+    if (sizeof(TKV) == 2 && (long long)R * g.n_kv_heads >= 384 &&
+        flash_prefill_supported(g.n_heads / g.n_kv_heads, g.max_context,
+                                (size_t)L.n_pages * 2 * g.n_kv_heads * kPage * kHeadDim)) {
+      for (int r = 0; r < R;) {
+        int e = r + 1;
+        while (e < R && rs[e] == rs[r]) ++e;
+        const int pairs = ((e - r + 31) / 32 + 1) / 2;
+        for (int k = 0; k < pairs; ++k) items.push_back(FlashItem{rs[r], rp[r], r, e - r, k});
+        r = e;
+      }
+      HIPCHK(c, hipMemcpyAsync(c->at<FlashItem>(L.items), items.data(), items.size() * sizeof(FlashItem),
+                               hipMemcpyHostToDevice, st));
+    }
     HIPCHK(c, hipMemcpyAsync(row_stream, rs.data(), R * sizeof(int), hipMemcpyHostToDevice, st));
     HIPCHK(c, hipMemcpyAsync(row_pos, rp.data(), R * sizeof(int), hipMemcpyHostToDevice, st));
     HIPCHK(c, hipMemcpyAsync(c->at<int>(L.feed), tk.data(), R * sizeof(int), hipMemcpyHostToDevice, st));
     DK::prep_embed(st, R, -2, c->at<int>(L.feed), row_stream, row_pos, c->at<int>(L.pos), c->at<int>(L.pending),
                    slot, c->at<TW>(L.embed), x, d);
-    enqueue_layers<TW, TKV, TM>(c, R, false, 1, -2, nullptr);
+    enqueue_layers<TW, TKV, TM>(c, R, false, 1, -2, nullptr, -1, 0, (int)items.size());
     if (ne > 0) {
-      // Last rows to rows 0 .. ne-1 (row i's source lies at or after row i
-      // and after every earlier destination), then the head and argmax.
-      for (int i = 0; i < ne; ++i)
-        if (last_r[i] != i)
-          HIPCHK(c, hipMemcpyAsync(x + (size_t)i * d, x + (size_t)last_r[i] * d, d * sizeof(float),
-                                   hipMemcpyDeviceToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(row_stream, last_s.data(), ne * sizeof(int), hipMemcpyHostToDevice, st));
-      HIPCHK(c, hipMemcpyAsync(row_pos, last_p.data(), ne * sizeof(int), hipMemcpyHostToDevice, st));
-      if (GK::norm_fusable(d)) GK::rmsnorm(st, ne, x, d, fn, g.rms_eps, h);
-      else DK::rmsnorm_rows(st, ne, x, fn, g.rms_eps, d, h);
+      // The streams whose last row the pass held: norm of those rows into
+      // rows 0 .. ne - 1 of h, then the head and argmax.
+      put_ints(st, row_stream, last_s.data(), ne);
+      put_ints(st, row_pos, last_p.data(), ne);
+      if (GK::norm_fusable(d)) {
+        put_ints(st, c->at<int>(L.feed), last_r.data(), ne);
+        GK::rmsnorm(st, ne, x, d, fn, g.rms_eps, h, c->at<int>(L.feed));
+      } else {
+        // Row i's source lies at or after row i and after every earlier
+        // destination.
+        for (int i = 0; i < ne; ++i)
+          if (last_r[i] != i)
+            HIPCHK(c, hipMemcpyAsync(x + (size_t)i * d, x + (size_t)last_r[i] * d, d * sizeof(float),
+                                     hipMemcpyDeviceToDevice, st));
+        DK::rmsnorm_rows(st, ne, x, fn, g.rms_eps, d, h);
+      }
       GK::logits(st, gws, h, ne, c->at<TM>(L.lm_headM), d, g.vocab, 1.f / c->wscale, nullptr, slot, row_stream,
                  L.wqkvT16.empty() ? nullptr : c->at<TM>(L.lm_headT16));
       finalize(st, 0, ne, row_stream, row_pos, slot, c->at<int>(L.pending), c->at<int>(L.hist), c->at<int>(L.pos),
@@ -785,13 +820,18 @@ hh_status do_decode(hh_ctx* c, int n, const std::vector<int>& ids, const int32_t
   return HH_OK;
 }
 
-hh_status reset_stream(hh_ctx* c, int s) {
-  for (int p : c->pages[s]) c->free_pages.push_back(p);
-  c->pages[s].clear();
-  c->len[s] = 0;
-  HIPCHK(c, hipMemsetAsync(c->at<int>(c->L.pos) + s, 0, sizeof(int), c->stream));
-  HIPCHK(c, hipMemsetAsync(c->at<int>(c->L.pending) + s, 0, sizeof(int), c->stream));
-  HIPCHK(c, hipMemsetAsync(c->at<unsigned long long>(c->L.slot) + s, 0, sizeof(unsigned long long), c->stream));
+// Streams [s0, s0 + n): pages back to the pool, lengths and device words to
+// zero in one launch (the decode-step kernel's error word with clear_error).
+hh_status reset_range(hh_ctx* c, int s0, int n, bool clear_error) {
+  for (int s = s0; s < s0 + n; ++s) {
+    for (int p : c->pages[s]) c->free_pages.push_back(p);
+    c->pages[s].clear();
+    c->len[s] = 0;
+  }
+  int* err = clear_error && c->step_wg > 0 ? reinterpret_cast<int*>(c->at<unsigned long long>(c->L.ll) + c->L.ll_words - 8) : nullptr;
+  reset_streams(c->stream, s0, n, c->at<int>(c->L.pos), c->at<int>(c->L.pending),
+                c->at<unsigned long long>(c->L.slot), err);
+  HIPCHK(c, hipGetLastError());
   return HH_OK;
 }
 
@@ -1019,10 +1059,8 @@ hh_status hh_load_weights(hh_ctx* c, const void* const* tensors, int32_t n_tenso
   }
   HIPCHK(c, hipGetLastError());
   HIPCHK(c, hipStreamSynchronize(st));
-  for (int s = 0; s < g.max_streams; ++s) {
-    hh_status rc = reset_stream(c, s);
-    if (rc != HH_OK) return rc;
-  }
+  const hh_status rc = reset_range(c, 0, g.max_streams, false);
+  if (rc != HH_OK) return rc;
   HIPCHK(c, hipStreamSynchronize(st));
   c->loaded = true;
   c->err.clear();
@@ -1155,16 +1193,9 @@ hh_status hh_decode_step_noalloc(hh_ctx* c, int32_t s, const int32_t* token, flo
 hh_status hh_reset(hh_ctx* c, int32_t s) {
   if (!c) return HH_ERR_INVALID_ARG;
   if (s < -1 || s >= c->cfg.max_streams) return c->fail(HH_ERR_INVALID_ARG, "stream id out of range");
-  for (int i = 0; i < c->cfg.max_streams; ++i)
-    if (s == -1 || s == i) {
-      hh_status rc = reset_stream(c, i);
-      if (rc != HH_OK) return rc;
-    }
-  // Clear the decode-step kernel's error word: later steps run again (a
-  // stream that recorded -1 keeps it as its pending token until reset).
-  if (c->step_wg > 0)
-    HIPCHK(c, hipMemsetAsync(c->at<unsigned long long>(c->L.ll) + c->L.ll_words - 8, 0, sizeof(int), c->stream));
-  return HH_OK;
+  // The error word goes with any reset: later steps run again (a stream that
+  // recorded -1 keeps it as its pending token until its own reset).
+  return s == -1 ? reset_range(c, 0, c->cfg.max_streams, true) : reset_range(c, s, 1, true);
 }
 
 hh_status hh_stream_length(const hh_ctx* c, int32_t s, int32_t* length) {
