@@ -79,61 +79,80 @@ struct EpiQKV {
       dst[i + 32] = (TKV)y1;
     }
   }
-  // Register epilogue: logical columns cb + c and cb + 32 + c (cb % 64 == 0).
-  __device__ void pair(int row, int cb, int c, float v0, float v1) const {
-    const int head = cb / 64;
-    if (head < hq + 2 * hkv) head_pair(row, head, c, v0, v1);
-  }
-  // A wave's whole in-range 64-column group (one head) for FM x 16 rows:
-  // element e of accumulator block i is row rb + 32 i + 8 (e / 4) + e % 4.
-  // The head's kind is decided once for all its rows.  Per block of 16 rows,
-  // every lookup (positions, rotations, KV pages) is loaded before any
-  // store: the stores may alias the tables as far as the compiler can tell,
-  // so interleaved they would serialise one round trip per element.
+  // Register epilogue of the tile kernel (see k_gemm_tile): the lane's rows
+  // row0 + 16 i < M, columns cb + 8 h .. + 8 and the same + 32 of the group of
+  // 64 at cb (one head, its kind the same for the whole wave).  A row's
+  // lookups are loaded before the previous row's stores: the stores may alias
+  // the tables as far as the compiler can tell, and would serialise one round
+  // trip per row.
   template <int FM>
-  __device__ void group_full(int rb, int cb, int c, const f32x16* a0, const f32x16* a1) const {
+  __device__ void tile(int row0, int cb, int h, int M, const f32x4 (&acc)[FM][4]) const {
     const int head = cb / 64;
+    if (head >= hq + 2 * hkv) return;
     const bool isq = head < hq, isk = !isq && head < hq + hkv;
     const int kvh = isq ? 0 : isk ? head - hq : head - hq - hkv;
+    int p[FM], pg[FM];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) p[i] = row_pos[min(row0 + 16 * i, M - 1)];
+    if (!isq) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) pg[i] = row_stream[min(row0 + 16 * i, M - 1)];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) pg[i] = page_table[(size_t)pg[i] * L.max_pages + p[i] / kPage];
+    }
+    f32x4 cs[2][4];  // (cos, sin) of pairs 8 h .. + 8
+    auto look = [&](f32x4* c, int pos) {
+      const f32x4* src = reinterpret_cast<const f32x4*>(rope + (size_t)pos * 32 + 8 * h);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) c[e] = src[e];
+    };
+    if (isq || isk) look(cs[0], p[0]);
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      int p[16], sr[16], pg[16];
-      float2 cs[16];
+      if (i + 1 < FM && (isq || isk)) look(cs[(i + 1) & 1], p[i + 1]);
+      f32x4 lo[2], hi[2];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = rb + 32 * i + 8 * (e >> 2) + (e & 3);
-        p[e] = row_pos[row];
-        if (!isq) sr[e] = row_stream[row];
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        cs[e] = isq || isk ? rope[(size_t)p[e] * 32 + c] : make_float2(1.f, 0.f);
-        if (!isq) pg[e] = page_table[(size_t)sr[e] * L.max_pages + p[e] / kPage];
-      }
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int row = rb + 32 * i + 8 * (e >> 2) + (e & 3);
-        float y0 = a0[i][e] * scale, y1 = a1[i][e] * scale;
+      for (int e = 0; e < 8; ++e) {
+        float y0 = acc[i][e >> 2][e & 3] * scale, y1 = acc[i][2 + (e >> 2)][e & 3] * scale;
         if (isq || isk) {
-          const float r0 = y0 * cs[e].x - y1 * cs[e].y, r1 = y1 * cs[e].x + y0 * cs[e].y;
+          const float c = cs[i & 1][e >> 1][2 * (e & 1)], sn = cs[i & 1][e >> 1][2 * (e & 1) + 1];
+          const float r0 = y0 * c - y1 * sn, r1 = y1 * c + y0 * sn;
           y0 = r0;
           y1 = r1;
         }
-        if (isq) {
-          const size_t o = ((size_t)row * hq + head) * 64 + c;
-          if (q) {
-            q[o] = y0;
-            q[o + 32] = y1;
+        lo[e >> 2][e & 3] = y0;
+        hi[e >> 2][e & 3] = y1;
+      }
+      const int row = row0 + 16 * i;
+      // (Every loaded value is used before the branch: one left pending on the
+      // path around it would be waited for in every step of the main loop.)
+      const size_t ko = isq ? 0 : L.head_tile(layer, pg[i], isk ? 0 : 1, kvh) + (p[i] % kPage) * 64 + 8 * h;
+      asm volatile("" ::"v"(ko), "v"(lo[0]), "v"(lo[1]), "v"(hi[0]), "v"(hi[1]));
+      if (row >= M) continue;
+      auto store = [&](TKV* dst) {
+        if constexpr (sizeof(TKV) == 2) {
+          f16x8 a, b;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            a[e] = (_Float16)lo[e >> 2][e & 3];
+            b[e] = (_Float16)hi[e >> 2][e & 3];
           }
-          if (qM) {
-            qM[o] = (TKV)y0;
-            qM[o + 32] = (TKV)y1;
-          }
-        } else {
-          TKV* dst = kv + L.head_tile(layer, pg[e], isk ? 0 : 1, kvh) + (p[e] % kPage) * 64 + c;
-          dst[0] = (TKV)y0;
-          dst[32] = (TKV)y1;
+          *reinterpret_cast<f16x8*>(dst) = a;
+          *reinterpret_cast<f16x8*>(dst + 32) = b;
         }
+      };
+      if (isq) {
+        const size_t o = ((size_t)row * hq + head) * 64 + 8 * h;
+        if (q) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            *reinterpret_cast<f32x4*>(q + o + 4 * e) = lo[e];
+            *reinterpret_cast<f32x4*>(q + o + 32 + 4 * e) = hi[e];
+          }
+        }
+        if (qM) store(qM + o);
+      } else {
+        store(kv + ko);
       }
     }
   }
@@ -183,21 +202,35 @@ struct EpiResid {
   float scale;
   float* x;
   __device__ int b_row(int n) const { return n < N ? n : -1; }
-  __device__ void pair(int row, int cb, int c, float v0, float v1) const {
-    float* xr = x + (size_t)row * N + cb + c;
-    if (cb + c < N) xr[0] += v0 * scale;
-    if (cb + 32 + c < N) xr[32] += v1 * scale;
-  }
+  // The next row's x is loaded before this row's stores.  N % 64 == 0.
   template <int FM>
-  __device__ void group_full(int rb, int cb, int c, const f32x16* a0, const f32x16* a1) const {
+  __device__ void tile(int row0, int cb, int h, int M, const f32x4 (&acc)[FM][4]) const {
+    if (cb >= N) return;
+    f32x4 v[2][4];
+    auto at = [&](int i, int j) {
+      return reinterpret_cast<f32x4*>(x + (size_t)min(row0 + 16 * i, M - 1) * N + cb + 32 * (j >> 1) + 8 * h + 4 * (j & 1));
+    };
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int j = 0; j < 4; ++j) v[0][j] = *at(0, j);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float* xr = x + (size_t)(rb + 32 * i + 8 * (e >> 2) + (e & 3)) * N + cb + c;
-        xr[0] += a0[i][e] * scale;
-        xr[32] += a1[i][e] * scale;
+    for (int i = 0; i < FM; ++i) {
+      if (i + 1 < FM) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[(i + 1) & 1][j] = *at(i + 1, j);
       }
+      // The sums before the branch: a load left pending on a path around its
+      // use would be waited for in every step of the main loop.
+      f32x4 t[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[j][e] = v[i & 1][j][e] + acc[i][j][e] * scale;
+      asm volatile("" ::"v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]));
+      if (row0 + 16 * i < M) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) *at(i, j) = t[j];
+      }
+    }
   }
   __device__ void operator()(const float* Cs, int ldc, int m0, int M, int n0, int BM, int BN) const {
     for (int idx = threadIdx.x; idx < BM * BN; idx += blockDim.x) {
@@ -219,24 +252,24 @@ struct EpiGateUp {
     const int c = n % (2 * half), j = (n / (2 * half)) * half + (c < half ? c : c - half);
     return j < F ? (c < half ? j : F + j) : -1;
   }
-  // Register epilogue (half == 32): gate column cb + c, up column cb + 32 + c.
-  __device__ void pair(int row, int cb, int c, float v0, float v1) const {
-    const int col = (cb / 64) * 32 + c;
-    if (col < F) m[(size_t)row * F + col] = (TM)(silu(v0 * scale) * (v1 * scale));
-  }
-  // In-range group; SiLU with the hardware reciprocal (the result is rounded
-  // to fp16 right after, far coarser than its 1-ulp error).
+  // Register epilogue (half == 32): gate columns cb + 8 h .. + 8, their up
+  // columns 32 later.  SiLU with the hardware reciprocal (the result is
+  // rounded to fp16 right after, far coarser than its 1-ulp error).
   template <int FM>
-  __device__ void group_full(int rb, int cb, int c, const f32x16* a0, const f32x16* a1) const {
-    TM* mc = m + (cb / 64) * 32 + c;
+  __device__ void tile(int row0, int cb, int h, int M, const f32x4 (&acc)[FM][4]) const {
+    const int col = (cb / 64) * 32 + 8 * h;
+    if (col >= F) return;  // F % 8 == 0
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+    for (int i = 0; i < FM; ++i) {
+      f16x8 o;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float gt = a0[i][e] * scale;
-        mc[(size_t)(rb + 32 * i + 8 * (e >> 2) + (e & 3)) * F] =
-            (TM)(gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * (a1[i][e] * scale));
+      for (int e = 0; e < 8; ++e) {
+        const float gt = acc[i][e >> 2][e & 3] * scale;
+        o[e] = (_Float16)(gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * (acc[i][2 + (e >> 2)][e & 3] * scale));
       }
+      const int row = row0 + 16 * i;
+      if (row < M) *reinterpret_cast<f16x8*>(m + (size_t)row * F + col) = o;
+    }
   }
   __device__ void operator()(const float* Cs, int ldc, int m0, int M, int n0, int BM, int BN) const {
     const int j0 = (n0 / (2 * half)) * half, nc = BN / 2;
@@ -250,22 +283,77 @@ struct EpiGateUp {
   }
 };
 
-// LM head rows: optional fp32 logits and the per-row packed argmax into the
-// row's stream slot.
+// LM head rows: optional fp32 logits, and the packed argmax of row slot_row (-1:
+// of every row) into the row's stream slot.  PAIR (tile kernel only): blocks
+// of 32 rows of A hold 16 rows' fp16 high parts and then their low parts,
+// scaled per row (k_norm_split): the two products are added and scaled back.
+template <bool PAIR>
 struct EpiLogits {
   int V;
   float scale;
   float* logits;
   unsigned long long* slot;
   const int* row_stream;
+  int slot_row;
+  const float* row_scale;  // PAIR: one factor per logical row
+  int rows;                // PAIR: logical rows
   __device__ int b_row(int n) const { return n < V ? n : -1; }
+  template <int FM>
+  __device__ void tile(int row0, int cb, int h, int M, const f32x4 (&acc)[FM][4]) const {
+    constexpr int STEP = PAIR ? 2 : 1;
+    const int l15 = threadIdx.x & 15;
+    const int nrows = PAIR ? rows : M;
+    const bool vec = V % 4 == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0;
+#pragma unroll
+    for (int i = 0; i < FM; i += STEP) {
+      // Every wave's block starts at a multiple of 32 rows of A.
+      const int row = PAIR ? ((row0 - l15) >> 1) + 8 * i + l15 : row0 + 16 * i;
+      const bool in = row < nrows;
+      const float f = PAIR ? scale * row_scale[in ? row : 0] : scale;
+      unsigned long long best = 0ull;
+      const bool keyed = slot && (slot_row < 0 || row == slot_row) && in;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int col = cb + 32 * (j >> 1) + 8 * h + 4 * (j & 1);
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (PAIR ? acc[i][j][e] + acc[i + STEP - 1][j][e] : acc[i][j][e]) * f;
+        if (logits && in) {
+          float* dst = logits + (size_t)row * V + col;
+          if (vec) {
+            if (col < V) *reinterpret_cast<f32x4*>(dst) = v;
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (col + e < V) dst[e] = v[e];
+          }
+        }
+        if (keyed) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const unsigned long long k = argmax_key(v[e], (uint32_t)(col + e));
+            if (col + e < V && k > best) best = k;
+          }
+        }
+      }
+      if (keyed) {
+        // The four lanes of a row are all in here together.
+        unsigned long long o = __shfl_xor(best, 16);
+        best = o > best ? o : best;
+        o = __shfl_xor(best, 32);
+        best = o > best ? o : best;
+        if (h == 0) atomicMax(slot + row_stream[row], best);
+      }
+    }
+  }
   __device__ void operator()(const float* Cs, int ldc, int m0, int M, int n0, int BM, int BN) const {
     if (logits)
       for (int idx = threadIdx.x; idx < BM * BN; idx += blockDim.x) {
         const int r = idx / BN, c = idx % BN, row = m0 + r, col = n0 + c;
         if (row < M && col < V) logits[(size_t)row * V + col] = Cs[r * ldc + c] * scale;
       }
-    if (slot && (int)threadIdx.x < BM && m0 + (int)threadIdx.x < M) {
+    if (slot && (int)threadIdx.x < BM && m0 + (int)threadIdx.x < M &&
+        (slot_row < 0 || m0 + (int)threadIdx.x == slot_row)) {
       const int r = threadIdx.x;
       unsigned long long best = 0ull;
       for (int c = 0; c < BN && n0 + c < V; ++c) {
@@ -568,172 +656,232 @@ __global__ __launch_bounds__(256) void k_splitk_finalize(const float* __restrict
   epi(Cs, LDC, m0, M, n0, kFinRows, BN);
 }
 
-// ---------------------------------------------------------------- wide-tile fp16 kernel (prompt prefill)
+// ---------------------------------------------------------------- tile kernel (prompt prefill)
 
-// Prompt-sized GEMMs (M >= 256): BM x BN x 64 tiles, one 256-thread workgroup
-// per CU, four waves in a 2 x 2 grid each owning a (BM/2) x (BN/2) block of
-// 32x32x16 MFMAs.  A wave's LDS traffic per MFMA falls with the size of its
-// block (a 128 x 128 block reads 8 KiB of fragments per 16 MFMAs, a 64 x 64
-// block 4 KiB per 4), so large wave blocks keep the LDS well below its
-// bandwidth.  Staging is the same as k_gemm_f16's (whole-line direct loads,
-// (row/2)-swizzled chunks), one barrier per K step: the loads of a step are
-// issued right after the barrier that retires the stage they overwrite.  The
-// epilogue runs from the accumulators: column pairs (c, c + 32) of a 64-column
-// group sit in one lane (blocks 2g and 2g + 1 of the wave), which is the pairing
-// every register epilogue needs (rotary halves, gate / up).
-template <int BM, int BN, int NW_ = 4>
-struct WideTile {
-  static constexpr int BK = 64, NW = NW_, THREADS = 64 * NW_;
-  // Wave grid: 2 x 2 with four waves; with eight (two per SIMD, so one
-  // wave's MFMAs run while the other waits on LDS or a barrier) 2 x 4 for
-  // 256-wide tiles, else 4 x 2, so a wave block keeps whole 64-column groups.
-  static constexpr int WGM = NW == 4 ? 2 : (BN >= 256 ? 2 : 4), WGN = NW / WGM;
-  static constexpr int WM = BM / WGM, WN = BN / WGN;  // wave block
-  static constexpr int FM = WM / 32, FN = WN / 32;   // 32x32 MFMA blocks per wave
-  static constexpr int GROUPS = (BM + BN) / 8;       // 1 KiB row groups per stage
-  static constexpr int NI = GROUPS / NW;             // load instructions per wave per stage
-  static constexpr int STAGE = GROUPS * 1024;
-  static constexpr int NSTAGE = (160 * 1024) / STAGE >= 3 ? 3 : 2;
-  static constexpr int LDS = NSTAGE * STAGE;
-  static_assert(FN % 2 == 0, "a wave block holds whole 64-column groups");
-  static_assert(GROUPS % NW == 0, "row groups split evenly over the waves");
-  static_assert(NSTAGE * STAGE <= 160 * 1024, "stages fit the LDS");
-  static_assert((NSTAGE - 1) * NI <= 63, "in-flight loads fit the vmcnt range");
+// Prompt-sized GEMMs (M >= 128): BM x BN x 64 tiles, eight waves, each a block
+// of WM x 64 outputs as 16x16x32 MFMAs with the weights as the first operand:
+// a lane's four results are then four consecutive columns of one row, and with
+// the weight rows of a fragment taken in the order 8(r/4) + 4(j%2) + r%4 of
+// each 32, two fragments give it eight, so every store is 16 bytes.
+//
+// What bounds it: with inputs of real spread the matrix cores run at the
+// card's power limit (8192 x 2048 x 8192: 138 us on zeros, 218 us on normal
+// draws, the same code), so what counts is the energy and the work beside the
+// MFMAs.  Against the kernel before (32x32x16 MFMAs, a workgroup per tile):
+// 16x16x32 forms move half the accumulator registers per product (gate/up at
+// 8192 rows 525 -> 505 us); one workgroup per CU walks the tiles of its XCD,
+// and its loads run on into the next tile (the load cursor below is NST steps
+// ahead of the MFMAs and knows nothing of tile ends), so neither the pipeline's
+// fill nor the epilogue's stores leave the matrix cores idle (505 -> 458 us,
+// 1,200 TFLOP/s).
+//
+// K steps go global -> LDS with direct 16-byte loads through NST stages, the
+// addresses in scalar registers (a row group's offset and the step's) but
+// for one lane offset per operand.  The fragments of a step's second half are
+// read under the first half's MFMAs, the next step's first half under the
+// second's; the one barrier per step stands where every wave holds its last
+// fragments of the stage that the loads behind the barrier refill.
+//
+// LDS holds 128-byte rows (64 k) of eight 16-byte chunks; row r's chunk c lies
+// at c ^ swz(r): the 16 rows of a fragment fall on 16 distinct quads of banks
+// with swz = (r/2) % 8 for the activations' 16 consecutive rows, and with
+// (r/2) % 2 + 2 ((r/8) % 4) for the weights' order above.
+//
+// XCDs: workgroups are dealt round-robin to the eight, and an XCD takes a run
+// of consecutive tiles, numbered down bands of 1,024 rows, so that its 32
+// workgroups share a few row and column tiles in its L2.
+template <int BM_, int BN_>
+struct Tile {
+  static constexpr int BM = BM_, BN = BN_, NW = 8, THREADS = 64 * NW;
+  static constexpr int WGN = BN / 64, WGM = NW / WGN, WM = BM / WGM;  // wave grid, rows per wave
+  static constexpr int FM = WM / 16, FN = 4;                          // 16 x 16 blocks per wave
+  static constexpr int NA = BM / 64, NB = BN / 64, NI = NA + NB;      // 8-row groups per wave and stage
+  static constexpr int STAGE = (BM + BN) * 128;
+  static constexpr int NST = (160 * 1024) / STAGE >= 3 ? 3 : 2;
+  static constexpr int LDS = NST * STAGE;
+  static_assert(WM % 32 == 0 && LDS <= 160 * 1024 && (NST - 1) * NI <= 63, "tile");
 };
 
-template <int BM, int BN, int NW, class Epi>
-__global__ __launch_bounds__(64 * NW, 1) void k_gemm_wide(const _Float16* __restrict__ A, int M,
-                                                          const _Float16* __restrict__ W, int K, int ntn, int ntiles,
-                                                          int steps_per_split, float* __restrict__ partial, int ncols,
-                                                          Epi epi) {
-  using T = WideTile<BM, BN, NW>;
+// One 16-byte direct buffer -> LDS load per lane (a device function for the
+// reason given at load_lds16).
+typedef __attribute__((address_space(3))) char lds_char;
+__device__ __forceinline__ void buffer_lds16(__amdgpu_buffer_rsrc_t r, lds_char* dst, int voff, unsigned soff) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff, soff, 0, 0);
+}
+
+template <int BM, int BN, class Epi>
+__global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict__ A, int M,
+                                                      const _Float16* __restrict__ W, int K, int ntm, int ntn,
+                                                      int splits, int steps_per_split, float* __restrict__ partial,
+                                                      int ncols, Epi epi) {
+  using T = Tile<BM, BN>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int tile = blockIdx.x % ntiles, split = blockIdx.x / ntiles;
-  const int tn = tile % ntn, tm = tile / ntn;
-  const int m0 = tm * BM, n0 = tn * BN;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int wm = wave / T::WGN, wn = wave % T::WGN;
-  const int nk_all = K / T::BK;
-  const int s0 = split * steps_per_split;
-  const int nk = min(nk_all, s0 + steps_per_split) - s0;
+  typedef __attribute__((address_space(3))) const f16x8 lds_f16x8;
+  const int tiles = ntm * ntn, units = tiles * splits;
+  const int per = (units + 7) / 8, hop = gridDim.x / 8, xcd = blockIdx.x & 7;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wm = wave / T::WGN, wn = wave % T::WGN, l15 = lane & 15, h = lane >> 4;
+  const int nk_all = K / 64;
+  const unsigned rowb = (unsigned)K * 2;
 
-  // Instruction q of wave w fills row group g = w + NW q (stage rows 8g .. 8g + 7):
-  // lane l takes row 8g + l/8, k chunk (l%8) ^ swz(row), swz(r) = (r/2) % 8.
-  const _Float16* src[T::NI];
+  // The unit'th piece of work of this workgroup: a tile and a K split.
+  struct Unit {
+    int m0, n0, split, s0, nk;
+  };
+  auto unit_at = [&](int idx, Unit& u) {
+    const int o = xcd * per + idx;
+    if (idx >= per || o >= units) return false;
+    constexpr int GM = 1024 / BM;
+    u.split = o / tiles;
+    const int t = o - u.split * tiles, band = t / (GM * ntn), r = t - band * GM * ntn, gm = min(GM, ntm - band * GM);
+    u.n0 = (r / gm) * BN;
+    u.m0 = (band * GM + r % gm) * BM;
+    u.s0 = u.split * steps_per_split;
+    u.nk = min(nk_all, u.s0 + steps_per_split) - u.s0;
+    return true;
+  };
+  int idx = blockIdx.x >> 3;
+  Unit u;
+  if (!unit_at(idx, u)) return;
+
+  // Load cursor: the next K step to load, on the tile it belongs to.  Wave w's
+  // instruction q fills row group g = w + 8 q (rows 8g .. 8g + 7, 1 KiB) of an
+  // operand.  Rows past M in a group that starts before M are outside the
+  // buffer's range (zeros); a group wholly past M, or past the columns, loads
+  // the tile's first rows instead.  Neither is ever stored.
+  int cidx = idx, ck = 0;
+  bool alive = true;
+  Unit cu = u;
+  const char *pa, *pw;
+  unsigned reca, oa[T::NA], ow[T::NB];
+  auto cursor_tile = [&]() {
+    pa = reinterpret_cast<const char*>(A) + ((size_t)cu.m0 * K + (size_t)cu.s0 * 64) * 2;
+    const int rows = min(M - cu.m0, BM);
+    reca = (unsigned)rows * rowb - (unsigned)cu.s0 * 128;
 #pragma unroll
-  for (int q = 0; q < T::NI; ++q) {
-    const int rr = 8 * (wave + T::NW * q) + (lane >> 3);
-    const int chunk = (lane & 7) ^ ((rr >> 1) & 7);
-    if (rr < BM) {
-      const int row = min(m0 + rr, M - 1);  // rows past M: computed, never stored
-      src[q] = A + (size_t)row * K + (size_t)s0 * T::BK + chunk * 8;
-    } else {
-      const int br = epi.b_row(n0 + rr - BM);
-      src[q] = W + (size_t)(br < 0 ? 0 : br) * K + (size_t)s0 * T::BK + chunk * 8;
+    for (int q = 0; q < T::NA; ++q) oa[q] = 8 * (wave + 8 * q) < rows ? (unsigned)(8 * (wave + 8 * q)) * rowb : 0u;
+    const int b0 = epi.b_row(cu.n0);
+    pw = reinterpret_cast<const char*>(W) + ((size_t)b0 * K + (size_t)cu.s0 * 64) * 2;
+#pragma unroll
+    for (int q = 0; q < T::NB; ++q) {
+      const int br = epi.b_row(cu.n0 + 8 * (wave + 8 * q));
+      ow[q] = br < 0 ? 0u : (unsigned)(br - b0) * rowb;
     }
-  }
-
-  f32x16 acc[T::FM][T::FN];
-#pragma unroll
-  for (int i = 0; i < T::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::FN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  // Loads are issued unconditionally (K steps past the end re-read the last
-  // one into a stage nobody reads again), so exactly NSTAGE - 2 stages are in
-  // flight behind the current one at every wait, and the scheduling groups
-  // below see one basic block per step.
-  constexpr int kWaitLds = 0xF | (0x7 << 4) | (0x3 << 14);  // lgkmcnt(0)
-#pragma unroll
-  for (int i = 0; i < T::NSTAGE - 1; ++i)
-    issue_stage<T::NI, T::NW>(src, min(i, nk - 1) * T::BK, smem + i * T::STAGE, wave);
-  for (int step = 0; step < nk; ++step) {
-    wait_stages<T::NI>(T::NSTAGE - 2);  // this wave's loads of `step` have landed
-    __builtin_amdgcn_s_waitcnt(kWaitLds);
-    bare_barrier();                     // every wave's have, and every wave is done with step - 1
-    const int ahead = step + T::NSTAGE - 1;
-    const char* sb = smem + (step % T::NSTAGE) * T::STAGE;
-    char* nb = smem + (ahead % T::NSTAGE) * T::STAGE;
-    const int koff = min(ahead, nk - 1) * T::BK;
-    auto frag = [&](int r0, int kb) {
-      const int r = r0 + (lane & 31), c = 2 * kb + (lane >> 5);
-      return *reinterpret_cast<const f16x8*>(sb + r * 128 + 16 * (c ^ ((r >> 1) & 7)));
-    };
-    // Fragments of k block kb + 1 are read while the MFMAs of kb run; the
-    // next stage's global loads are spread over the step's MFMAs.
-    f16x8 a[2][T::FM], b[2][T::FN];
-#pragma unroll
-    for (int i = 0; i < T::FM; ++i) a[0][i] = frag(wm * T::WM + i * 32, 0);
-#pragma unroll
-    for (int j = 0; j < T::FN; ++j) b[0][j] = frag(BM + wn * T::WN + j * 32, 0);
-    constexpr int kLoadsPerKb = (T::NI + 3) / 4;
-#pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const int cur = kb & 1, nxt = cur ^ 1;
-      if (kb < 3) {
-#pragma unroll
-        for (int i = 0; i < T::FM; ++i) a[nxt][i] = frag(wm * T::WM + i * 32, kb + 1);
-#pragma unroll
-        for (int j = 0; j < T::FN; ++j) b[nxt][j] = frag(BM + wn * T::WN + j * 32, kb + 1);
-      }
-#pragma unroll
-      for (int q = kb * kLoadsPerKb; q < (kb + 1) * kLoadsPerKb && q < T::NI; ++q)
-        load_lds16(src[q] + koff, nb + (wave + T::NW * q) * 1024);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int i = 0; i < T::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < T::FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[cur][i], b[cur][j], acc[i][j], 0, 0, 0);
-      // Keep the reads and loads of this block ahead of its MFMAs (the
-      // scheduler would otherwise sink each read to just before its first use).
-      __builtin_amdgcn_sched_barrier(0);
+    ck = cu.nk;
+  };
+  auto cursor_next = [&]() {
+    if (!alive) return;
+    if (--ck > 0) {
+      pa += 128;
+      pw += 128;
+      reca -= 128;
+      return;
     }
+    cidx += hop;
+    alive = unit_at(cidx, cu);  // past the last unit: the last step again, into stages nobody reads
+    if (alive) cursor_tile();
+  };
+  cursor_tile();
+  const int va = (lane >> 3) * (int)rowb + 16 * ((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7));
+  const int vb = (lane >> 3) * (int)rowb + 16 * ((lane & 7) ^ (((lane >> 4) & 1) | ((wave & 3) << 1)));
+  auto issue = [&](unsigned so) {
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc((void*)pa, (short)0, (int)reca, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)pw, (short)0, -1, 0x00020000);
+    lds_char* dst = (lds_char*)smem + so + wave * 1024;
+#pragma unroll
+    for (int q = 0; q < T::NA; ++q) buffer_lds16(ra, dst + 8192 * q, va, oa[q]);
+#pragma unroll
+    for (int q = 0; q < T::NB; ++q) buffer_lds16(rw, dst + BM * 128 + 8192 * q, vb, ow[q]);
+  };
+
+  // Fragment addresses of the two 32-wide halves of a step.
+  int fa[2], fw[2];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) {
+    fa[kb] = (wm * T::WM + l15) * 128 + 16 * ((4 * kb + h) ^ (l15 >> 1));
+    fw[kb] = (BM + wn * 64 + 8 * (l15 >> 2) + (l15 & 3)) * 128 +
+             16 * ((4 * kb + h) ^ (((l15 >> 1) & 1) | ((l15 >> 2) << 1)));
   }
-  wait_stages<T::NI>(0);  // no direct-to-LDS load outlives the workgroup
-  // Element e of lane l in a 32x32 block: row 8(e/4) + 4(l/32) + e%4, column l%32.
-  const int rbase = m0 + wm * T::WM + 4 * (lane >> 5), c = lane & 31;
-  if (partial) {
-    float* dst = partial + (size_t)split * M * ncols;
+  f32x4 acc[T::FM][T::FN];
+  f16x8 a[2][T::FM], b[2][T::FN];
+  auto frags = [&](int kb, unsigned so) {
+    const lds_char* base = (const lds_char*)smem + so;
+#pragma unroll
+    for (int j = 0; j < T::FN; ++j) b[kb][j] = *(lds_f16x8*)(base + fw[kb] + (j >> 1) * 4096 + (j & 1) * 512);
+#pragma unroll
+    for (int i = 0; i < T::FM; ++i) a[kb][i] = *(lds_f16x8*)(base + fa[kb] + i * 2048);
+  };
+  auto mma = [&](int kb) {
 #pragma unroll
     for (int i = 0; i < T::FM; ++i)
 #pragma unroll
       for (int j = 0; j < T::FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b[kb][j], a[kb][i], acc[i][j], 0, 0, 0);
+  };
+  constexpr int NRD = T::FM + T::FN;
+  constexpr int kWaitLds = 0xF | (0x7 << 4) | (0x3 << 14);  // lgkmcnt(0)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int r = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-          const int col = n0 + wn * T::WN + j * 32 + c;
-          if (r < M && col < ncols) dst[(size_t)r * ncols + col] = acc[i][j][e];
-        }
-    return;
+  for (int s = 0; s < T::NST; ++s) {
+    issue(s * T::STAGE);
+    cursor_next();
   }
-  if (m0 + BM <= M && n0 + BN <= ncols) {
-    // Whole tile in range (every tile of a prompt whose length is a multiple
-    // of BM): no per-element guards, which would otherwise turn the unrolled
-    // epilogue into thousands of exec-mask branches.
+  unsigned so = 0;
+  wait_stages<T::NI>(T::NST - 1);
+  bare_barrier();
+  frags(0, 0);
+  while (true) {
 #pragma unroll
-    for (int g = 0; g < T::FN / 2; ++g) {
-      f32x16 a0[T::FM], a1[T::FM];
+    for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-      for (int i = 0; i < T::FM; ++i) {
-        a0[i] = acc[i][2 * g];
-        a1[i] = acc[i][2 * g + 1];
+      for (int j = 0; j < T::FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int step = 0; step < u.nk; ++step) {
+      const unsigned sn = so + T::STAGE == T::LDS ? 0u : so + T::STAGE;
+      __builtin_amdgcn_sched_barrier(0);
+      frags(1, so);
+      mma(0);
+#pragma unroll
+      for (int k = 0; k < NRD; ++k) {  // MFMA, read, MFMA, read, ...
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
-      epi.template group_full<T::FM>(rbase, n0 + wn * T::WN + 64 * g, c, a0, a1);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(kWaitLds);  // this wave has its last fragments of the stage
+      wait_stages<T::NI>(T::NST - 2);        // and its loads of the next step have landed
+      bare_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      frags(0, sn);
+      issue(so);
+      mma(1);
+#pragma unroll
+      for (int k = 0; k < (T::NI > NRD ? T::NI : NRD); ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (k < T::NI) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        if (k < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      cursor_next();
+      so = sn;
     }
-    return;
-  }
+    const int row0 = u.m0 + wm * T::WM + l15, cb = u.n0 + wn * 64;
+    if (partial) {
+      float* dst = partial + (size_t)u.split * M * ncols;
+      if (cb < ncols) {  // ncols % 64 == 0
 #pragma unroll
-  for (int i = 0; i < T::FM; ++i)
+        for (int i = 0; i < T::FM; ++i)
+          if (row0 + 16 * i < M) {
 #pragma unroll
-    for (int g = 0; g < T::FN / 2; ++g)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int r = rbase + i * 32 + 8 * (e >> 2) + (e & 3);
-        if (r < M) epi.pair(r, n0 + wn * T::WN + 64 * g, c, acc[i][2 * g][e], acc[i][2 * g + 1][e]);
+            for (int j = 0; j < T::FN; ++j)
+              *reinterpret_cast<f32x4*>(dst + (size_t)(row0 + 16 * i) * ncols + cb + 32 * (j >> 1) + 8 * h + 4 * (j & 1)) =
+                  acc[i][j];
+          }
       }
+    } else {
+      epi.template tile<T::FM>(row0, cb, h, M, acc);
+    }
+    idx += hop;
+    if (!unit_at(idx, u)) break;
+  }
+  wait_stages<T::NI>(0);  // no direct-to-LDS load outlives the workgroup
 }
 
 // ---------------------------------------------------------------- launchers
@@ -768,29 +916,30 @@ static int launch_f16(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M
   return splits;
 }
 
-template <int BM, int BN, int NW = 4, class Epi>
-static int launch_wide(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* W, int K, int n_cols,
+template <int BM, int BN, class Epi>
+static int launch_tile(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* W, int K, int n_cols,
                        int splits, const Epi& e, bool defer) {
-  using T = WideTile<BM, BN, NW>;
+  using T = Tile<BM, BN>;
   static bool attr = false;
   if (!attr) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_wide<BM, BN, NW, Epi>),
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_tile<BM, BN, Epi>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
     attr = true;
   }
-  const int ntn = (n_cols + BN - 1) / BN;
-  const int ntiles = ((M + BM - 1) / BM) * ntn;
-  const int nk = K / T::BK;
+  const int ntn = (n_cols + BN - 1) / BN, ntm = (M + BM - 1) / BM;
+  const int nk = K / 64;
   splits = std::max(1, std::min(splits, nk / 4));
   while (splits > 1 && (size_t)splits * M * n_cols * sizeof(float) > ws.bytes) --splits;
   const int per = (nk + splits - 1) / splits;
   splits = (nk + per - 1) / per;
   float* part = splits > 1 ? ws.ptr : nullptr;
-  k_gemm_wide<BM, BN, NW, Epi><<<ntiles * splits, T::THREADS, T::LDS, st>>>(A, M, W, K, ntn, ntiles, per, part, n_cols,
-                                                                            e);
-  if (splits > 1 && !defer)
-    k_splitk_finalize<Epi><<<((M + kFinRows - 1) / kFinRows) * ntn * (BN / 128), 256, 0, st>>>(part, splits, M, n_cols,
-                                                                                             ntn * (BN / 128), e);
+  // One workgroup per CU, the same number on each XCD.
+  const int grid = 8 * std::min((ntm * ntn * splits + 7) / 8, 256 / 8);
+  k_gemm_tile<BM, BN, Epi><<<grid, T::THREADS, T::LDS, st>>>(A, M, W, K, ntm, ntn, splits, per, part, n_cols, e);
+  if (splits > 1 && !defer) {
+    const int nf = (n_cols + 127) / 128;
+    k_splitk_finalize<Epi><<<((M + kFinRows - 1) / kFinRows) * nf, 256, 0, st>>>(part, splits, M, n_cols, nf, e);
+  }
   return splits;
 }
 
@@ -1221,7 +1370,7 @@ static bool skinny_res_go(hipStream_t st, unsigned bytes, const _Float16* A, int
 template <class Epi>
 static bool launch_skinny_res(hipStream_t st, const _Float16* A, int M, const _Float16* Wt, int K, int nb, int splits,
                               int per, float* part, int n_cols, int kw, const Epi& e, const RowNorm& rn) {
-  if constexpr (std::is_same<Epi, EpiLogits>::value) {
+  if constexpr (std::is_same<Epi, EpiLogits<false>>::value) {
     return false;
   } else {
     const char* v = getenv("HH_SKINNY_RES");
@@ -1307,64 +1456,72 @@ __global__ __launch_bounds__(256) void k_rownorm_apply(_Float16* __restrict__ A,
 // Tile choice of a prompt-sized GEMM: {BM, BN, splits}, BM == 0 for the
 // small-tile kernel.  HH_GEMM_QKV / _RESID (O projection) / _DOWN / _GATEUP =
 // "BMxBNxS" (or "0") overrides it, for tuning.
-struct WideCfg {
-  int bm, bn, splits, nw;  // nw: waves per workgroup (4 or 8)
+struct TileCfg {
+  int bm, bn, splits;
 };
 
-static WideCfg wide_choice(GemmKind kind, int M, int n_cols, int K) {
+static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
   static const char* names[4] = {"HH_GEMM_QKV", "HH_GEMM_RESID", "HH_GEMM_GATEUP", "HH_GEMM_LOGITS"};
   // The down projection (K > N) has a knob of its own.
   const char* env = getenv(kind == GemmKind::Resid && K > n_cols ? "HH_GEMM_DOWN" : names[(int)kind]);
   if (env) {
-    WideCfg c{0, 0, 1, 4};
-    if (sscanf(env, "%dx%dx%dx%d", &c.bm, &c.bn, &c.splits, &c.nw) >= 2) return c;
-    return WideCfg{0, 0, 1, 4};
+    TileCfg c{0, 0, 1};
+    if (sscanf(env, "%dx%dx%d", &c.bm, &c.bn, &c.splits) >= 2) return c;
+    return TileCfg{0, 0, 1};
   }
-  // Measured on the 1B prompt shapes (d 2048, FFN 8192): gate/up at 1024 rows
-  // takes 256 x 128 tiles (512 tiles, two rounds of the CUs; TTFT 3.74 ->
-  // 3.44 ms against 256 x 256, one tile per CU); the down and O projections
-  // (only 128 tiles of 128 x 128) gain most from a 2-way K split; everything
-  // at 256 rows stays on the small-tile kernel, whose two workgroups per CU
-  // suit these few-tile shapes better.
-  if (kind == GemmKind::GateUp && n_cols >= 8192) {
-    // Eight waves (two per SIMD) here: TTFT at 1024 rows 3.66 -> 3.57 ms;
-    // every other shape was slower with eight.
-    if (M >= 512) return WideCfg{256, 128, 1, 8};
-    if (M >= 256) return WideCfg{128, 128, 1, 4};
-  }
-  // O and down at >= 512 rows: 128 x 128 tiles, 2-way K split, eight waves
-  // (O 17.5 -> 16.3 us, down 45.6 -> 44.2 us at 1024 rows against four).
-  if (kind == GemmKind::Resid && M >= 512) return WideCfg{128, 128, 2, 8};
-  // QKV at >= 512 rows: 128 x 128 tiles, no split (its epilogue loads its
-  // rotations and KV pages ahead of the stores): TTFT at 1024 rows 3.41 ->
-  // 3.34 ms against the small-tile kernel, which stays better at 256 rows;
-  // eight waves 29.3 -> 28.1 us.
-  if (kind == GemmKind::QKV && M >= 512) return WideCfg{128, 128, 1, 8};
-  // QKV at 256 .. 511 rows: the same tiles with a 4-way K split (192
-  // workgroups; the split-K reduction applies the epilogue): TTFT at 256
-  // rows 1.68-1.69 -> 1.64 ms against the small-tile kernel's 3-way split
-  // (2-, 3- and 6-way splits, four waves and 128 x 256 tiles all slower).
-  if (kind == GemmKind::QKV && M >= 256) return WideCfg{128, 128, 4, 8};
-  return WideCfg{0, 0, 1, 4};
+  // Below 512 rows (1B shapes; us a layer at 256 rows, tiles / the small-tile
+  // kernel): two or more row tiles of gate/up 26.9 / 33.6; the down
+  // projection with K split over 256 workgroups 18.6 / 20.8; QKV from 256 rows
+  // with a 4-way split (its reduction applies the epilogue), 13.6 + 6.6 / 15 + 6;
+  // O stays with the small tiles (13.4 / 8.7: few steps, and two workgroups a
+  // CU hide each other's start).
+  if (kind == GemmKind::GateUp && (n_cols < 8192 || M <= 128)) return TileCfg{0, 0, 1};
+  if (kind == GemmKind::QKV && M < 512) return M >= 256 ? TileCfg{128, 128, 4} : TileCfg{0, 0, 1};
+  if (kind == GemmKind::Resid && M < 512 && (K < 4096 || M <= 128)) return TileCfg{0, 0, 1};
+  if (kind == GemmKind::Logits) return TileCfg{0, 0, 1};
+  // From there, the smallest of rounds x (steps x step + tail), where a round
+  // is a unit (tile, K split) on each of the 256 CUs; plus writing and
+  // reading back the partials of a split.  step and tail (us) are fits to the
+  // products of the 1B layer at 512 .. 8,192 rows, and the choices they give
+  // are the fastest measured there or within 3 %: gate/up 256 x 256 from 1,024
+  // rows (8,192 rows: 256 x 256 448, 256 x 128 509 us; 1,024: 65 and 69) and
+  // 256 x 128 at 512 (37.5; 256 x 256 on half the CUs 56); QKV 128 x 128 to
+  // 1,024 rows and 256 x 128 above (8,192: 114, 256 x 256 132, 128 x 128
+  // 134); down 8,192 rows 256 x 256 236 (128 x 128 302), 1,024 rows 128 x 128
+  // in two splits 47.
+  struct Cand {
+    int bm, bn;
+    double step, tail, tail_qkv;
+  };
+  static const Cand cands[3] = {{256, 256, 1.60, 4.7, 16.0}, {256, 128, 0.95, 2.3, 7.0}, {128, 128, 0.58, 1.4, 4.0}};
+  TileCfg best{0, 0, 1};
+  double least = 1e30;
+  for (const Cand& c : cands)
+    for (int splits = 1; splits <= (kind == GemmKind::Resid ? 8 : 1); splits *= 2) {
+      const int nk = K / 64;
+      if (splits > 1 && nk / splits < 4) break;
+      const long long units = (long long)((M + c.bm - 1) / c.bm) * ((n_cols + c.bn - 1) / c.bn) * splits;
+      const double t = (double)((units + 255) / 256) *
+                           ((double)((nk + splits - 1) / splits) * c.step + (kind == GemmKind::QKV ? c.tail_qkv : c.tail)) +
+                       (splits > 1 ? 0.37e-6 * 4.0 * splits * (double)M * n_cols : 0.0);
+      if (t < least) {
+        least = t;
+        best = TileCfg{c.bm, c.bn, splits};
+      }
+    }
+  return best;
 }
 
 // Returns the splits used, 0 when the shape is left to the small-tile kernel.
 template <class Epi>
-static int run_wide(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* W, int K, int n_cols,
+static int run_tile(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* W, int K, int n_cols,
                     const Epi& e, GemmKind kind, bool defer) {
-  if (kind == GemmKind::Logits || M < 128) return 0;
-  const WideCfg c = wide_choice(kind, M, n_cols, K);
-  if (c.nw == 8) {
-    if (c.bm == 256 && c.bn == 256) return launch_wide<256, 256, 8>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-    if (c.bm == 256 && c.bn == 128) return launch_wide<256, 128, 8>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-    if (c.bm == 128 && c.bn == 256) return launch_wide<128, 256, 8>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-    if (c.bm == 128 && c.bn == 128) return launch_wide<128, 128, 8>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-    return 0;
-  }
-  if (c.bm == 256 && c.bn == 256) return launch_wide<256, 256>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-  if (c.bm == 256 && c.bn == 128) return launch_wide<256, 128>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-  if (c.bm == 128 && c.bn == 256) return launch_wide<128, 256>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-  if (c.bm == 128 && c.bn == 128) return launch_wide<128, 128>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
+  if (M < 128) return 0;
+  const TileCfg c = tile_choice(kind, M, n_cols, K);
+  if (c.bm == 256 && c.bn == 256) return launch_tile<256, 256>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
+  if (c.bm == 256 && c.bn == 128) return launch_tile<256, 128>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
+  if (c.bm == 128 && c.bn == 256) return launch_tile<128, 256>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
+  if (c.bm == 128 && c.bn == 128) return launch_tile<128, 128>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
   return 0;
 }
 
@@ -1389,8 +1546,8 @@ static int run_gemm(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const 
     if (K % 64 == 0) {
       const _Float16* Ah = reinterpret_cast<const _Float16*>(A);
       const _Float16* Wh = reinterpret_cast<const _Float16*>(W);
-      if constexpr (!std::is_same<Epi, EpiLogits>::value) {
-        const int sp = run_wide(st, ws, Ah, M, Wh, K, n_cols, e, kind, defer);
+      if constexpr (!std::is_same<Epi, EpiLogits<false>>::value) {
+        const int sp = run_tile(st, ws, Ah, M, Wh, K, n_cols, e, kind, defer);
         if (sp > 0) return sp;
       }
       const long long ntn = (n_cols + 127) / 128;
@@ -1542,7 +1699,7 @@ template <typename TM, typename TKV>
 void GemmKernels<TM, TKV>::logits(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int V, float scale,
                                   float* logits, unsigned long long* slot, const int* row_stream, const TM* Wt,
                                   const RowNorm& rn) {
-  EpiLogits e{V, scale, logits, slot, row_stream};
+  EpiLogits<false> e{V, scale, logits, slot, row_stream, -1, nullptr, 0};
   run_gemm<TM>(st, ws, A, M, W, d, V, e, GemmKind::Logits, false, Wt, rn);
 }
 
