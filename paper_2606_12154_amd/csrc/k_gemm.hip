@@ -1460,35 +1460,17 @@ struct TileCfg {
   int bm, bn, splits;
 };
 
-static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
-  static const char* names[4] = {"HH_GEMM_QKV", "HH_GEMM_RESID", "HH_GEMM_GATEUP", "HH_GEMM_LOGITS"};
-  // The down projection (K > N) has a knob of its own.
-  const char* env = getenv(kind == GemmKind::Resid && K > n_cols ? "HH_GEMM_DOWN" : names[(int)kind]);
-  if (env) {
-    TileCfg c{0, 0, 1};
-    if (sscanf(env, "%dx%dx%d", &c.bm, &c.bn, &c.splits) >= 2) return c;
-    return TileCfg{0, 0, 1};
-  }
-  // Below 512 rows (1B shapes; us a layer at 256 rows, tiles / the small-tile
-  // kernel): two or more row tiles of gate/up 26.9 / 33.6; the down
-  // projection with K split over 256 workgroups 18.6 / 20.8; QKV from 256 rows
-  // with a 4-way split (its reduction applies the epilogue), 13.6 + 6.6 / 15 + 6;
-  // O stays with the small tiles (13.4 / 8.7: few steps, and two workgroups a
-  // CU hide each other's start).
-  if (kind == GemmKind::GateUp && (n_cols < 8192 || M <= 128)) return TileCfg{0, 0, 1};
-  if (kind == GemmKind::QKV && M < 512) return M >= 256 ? TileCfg{128, 128, 4} : TileCfg{0, 0, 1};
-  if (kind == GemmKind::Resid && M < 512 && (K < 4096 || M <= 128)) return TileCfg{0, 0, 1};
-  if (kind == GemmKind::Logits) return TileCfg{0, 0, 1};
-  // From there, the smallest of rounds x (steps x step + tail), where a round
-  // is a unit (tile, K split) on each of the 256 CUs; plus writing and
-  // reading back the partials of a split.  step and tail (us) are fits to the
-  // products of the 1B layer at 512 .. 8,192 rows, and the choices they give
-  // are the fastest measured there or within 3 %: gate/up 256 x 256 from 1,024
-  // rows (8,192 rows: 256 x 256 448, 256 x 128 509 us; 1,024: 65 and 69) and
-  // 256 x 128 at 512 (37.5; 256 x 256 on half the CUs 56); QKV 128 x 128 to
-  // 1,024 rows and 256 x 128 above (8,192: 114, 256 x 256 132, 128 x 128
-  // 134); down 8,192 rows 256 x 256 236 (128 x 128 302), 1,024 rows 128 x 128
-  // in two splits 47.
+// The tile and K splits (a power of two up to max_splits) of least estimated
+// time: rounds x (steps x step + tail), where a round is a unit (tile, K split)
+// on each of the 256 CUs, plus writing and reading back the partials of a
+// split.  step and tail (us) are fits to the products of the 1B layer at 512 ..
+// 8,192 rows, and the choices they give are the fastest measured there or
+// within 3 %: gate/up 256 x 256 from 1,024 rows (8,192 rows: 256 x 256 448, 256
+// x 128 509 us; 1,024: 65 and 69) and 256 x 128 at 512 (37.5; 256 x 256 on half
+// the CUs 56); QKV 128 x 128 to 1,024 rows and 256 x 128 above (8,192: 114, 256
+// x 256 132, 128 x 128 134); down 8,192 rows 256 x 256 236 (128 x 128 302),
+// 1,024 rows 128 x 128 in two splits 47.
+static TileCfg fit_tile(GemmKind kind, int M, int n_cols, int K, int max_splits) {
   struct Cand {
     int bm, bn;
     double step, tail, tail_qkv;
@@ -1497,7 +1479,7 @@ static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
   TileCfg best{0, 0, 1};
   double least = 1e30;
   for (const Cand& c : cands)
-    for (int splits = 1; splits <= (kind == GemmKind::Resid ? 8 : 1); splits *= 2) {
+    for (int splits = 1; splits <= max_splits; splits *= 2) {
       const int nk = K / 64;
       if (splits > 1 && nk / splits < 4) break;
       const long long units = (long long)((M + c.bm - 1) / c.bm) * ((n_cols + c.bn - 1) / c.bn) * splits;
@@ -1510,6 +1492,28 @@ static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
       }
     }
   return best;
+}
+
+static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
+  static const char* names[4] = {"HH_GEMM_QKV", "HH_GEMM_RESID", "HH_GEMM_GATEUP", "HH_GEMM_LOGITS"};
+  // The down projection (K > N) has a knob of its own.
+  const char* env = getenv(kind == GemmKind::Resid && K > n_cols ? "HH_GEMM_DOWN" : names[(int)kind]);
+  if (env) {
+    TileCfg c{0, 0, 1};
+    if (sscanf(env, "%dx%dx%d", &c.bm, &c.bn, &c.splits) < 2) return TileCfg{0, 0, 1};
+    if (kind == GemmKind::Logits) c.splits = 1;  // partials have whole groups of 64 columns
+    return c;
+  }
+  // Below 512 rows (1B shapes; us a layer at 256 rows, tiles / the small-tile
+  // kernel): two or more row tiles of gate/up 26.9 / 33.6; the down
+  // projection with K split over 256 workgroups 18.6 / 20.8; QKV from 256 rows
+  // with a 4-way split (its reduction applies the epilogue), 13.6 + 6.6 / 15 + 6;
+  // O stays with the small tiles (13.4 / 8.7: few steps, and two workgroups a
+  // CU hide each other's start).
+  if (kind == GemmKind::GateUp && (n_cols < 8192 || M <= 128)) return TileCfg{0, 0, 1};
+  if (kind == GemmKind::QKV && M < 512) return M >= 256 ? TileCfg{128, 128, 4} : TileCfg{0, 0, 1};
+  if (kind == GemmKind::Resid && M < 512 && (K < 4096 || M <= 128)) return TileCfg{0, 0, 1};
+  return fit_tile(kind, M, n_cols, K, kind == GemmKind::Resid ? 8 : 1);
 }
 
 // Returns the splits used, 0 when the shape is left to the small-tile kernel.
@@ -1546,10 +1550,8 @@ static int run_gemm(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const 
     if (K % 64 == 0) {
       const _Float16* Ah = reinterpret_cast<const _Float16*>(A);
       const _Float16* Wh = reinterpret_cast<const _Float16*>(W);
-      if constexpr (!std::is_same<Epi, EpiLogits<false>>::value) {
-        const int sp = run_tile(st, ws, Ah, M, Wh, K, n_cols, e, kind, defer);
-        if (sp > 0) return sp;
-      }
+      const int sp = run_tile(st, ws, Ah, M, Wh, K, n_cols, e, kind, defer);
+      if (sp > 0) return sp;
       const long long ntn = (n_cols + 127) / 128;
       if (M <= 32) return launch_f16<32>(st, ws, Ah, M, Wh, K, n_cols, e, defer);
       if (M <= 64 || ((M + 127) / 128) * ntn < 256) return launch_f16<64>(st, ws, Ah, M, Wh, K, n_cols, e, defer);
@@ -1698,9 +1700,64 @@ void GemmKernels<TM, TKV>::gateup(hipStream_t st, GemmWorkspace ws, const TM* A,
 template <typename TM, typename TKV>
 void GemmKernels<TM, TKV>::logits(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int V, float scale,
                                   float* logits, unsigned long long* slot, const int* row_stream, const TM* Wt,
-                                  const RowNorm& rn) {
-  EpiLogits<false> e{V, scale, logits, slot, row_stream, -1, nullptr, 0};
+                                  const RowNorm& rn, int slot_row) {
+  EpiLogits<false> e{V, scale, logits, slot, row_stream, slot_row, nullptr, 0};
   run_gemm<TM>(st, ws, A, M, W, d, V, e, GemmKind::Logits, false, Wt, rn);
+}
+
+// ---------------------------------------------------------------- LM head of many rows
+
+// Final RMSNorm of one row per workgroup into fp16 high and low parts: row r of
+// x goes to rows 32 (r / 16) + r % 16 and + 16 of out, times the power of two
+// that puts its largest value in [2^13, 2^14) (row_scale[r]: the inverse), so
+// the low parts keep 22 bits of the row's largest value whatever its size.
+__global__ __launch_bounds__(256) void k_norm_split(const float* __restrict__ x, int N, const float* __restrict__ gain,
+                                                    float eps, _Float16* __restrict__ out,
+                                                    float* __restrict__ row_scale) {
+  __shared__ float red[4];
+  const int row = blockIdx.x;
+  const float* xr = x + (size_t)row * N;
+  float ss = 0.f;
+  for (int k = threadIdx.x; k < N; k += 256) ss += xr[k] * xr[k];
+  const float inv = rsqrtf(block_sum256(ss, red) / (float)N + eps);
+  float mx = 0.f;
+  for (int k = threadIdx.x; k < N; k += 256) mx = fmaxf(mx, fabsf(xr[k] * inv * gain[k]));
+  mx = wave_max(mx);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  int e = 0;  // mx = f 2^e, f in [0.5, 1)
+  if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &e);
+  const float up = ldexpf(1.f, min(14 - e, 126));
+  if (threadIdx.x == 0) row_scale[row] = 1.f / up;
+  _Float16* hi = out + (size_t)(32 * (row >> 4) + (row & 15)) * N;
+  _Float16* lo = hi + (size_t)16 * N;
+  for (int k = threadIdx.x; k < N; k += 256) {
+    const float v = xr[k] * inv * gain[k] * up;
+    const _Float16 a = (_Float16)v;
+    hi[k] = a;
+    lo[k] = (_Float16)(v - (float)a);
+  }
+}
+
+// A row's logits were 32-bit products of the row with the weights, one pass
+// over the LM head per row (84 us each on the 1B model).  Two fp16 terms per
+// value keep that precision on the matrix cores, and the rows share the pass.
+template <typename TM, typename TKV>
+void GemmKernels<TM, TKV>::logits_split(hipStream_t st, const float* x, int M, const float* gain, float eps,
+                                        _Float16* split, float* row_scale, const TM* W, int d, int V, float scale,
+                                        float* logits, unsigned long long* slot, const int* row_stream, int slot_row) {
+  if constexpr (sizeof(TM) == 2) {
+    k_norm_split<<<M, 256, 0, st>>>(x, d, gain, eps, split, row_scale);
+    EpiLogits<true> e{V, scale, logits, slot, row_stream, slot_row, row_scale, M};
+    const int rows = 32 * ((M + 15) / 16);
+    const TileCfg c = fit_tile(GemmKind::Logits, rows, V, d, 1);
+    const GemmWorkspace none{nullptr, 0};
+    const _Float16* Wh = reinterpret_cast<const _Float16*>(W);
+    if (c.bm == 256 && c.bn == 256) launch_tile<256, 256>(st, none, split, rows, Wh, d, V, 1, e, true);
+    else if (c.bm == 256) launch_tile<256, 128>(st, none, split, rows, Wh, d, V, 1, e, true);
+    else launch_tile<128, 128>(st, none, split, rows, Wh, d, V, 1, e, true);
+  }
 }
 
 template struct GemmKernels<float, float>;

@@ -26,6 +26,7 @@ namespace {
 
 constexpr int kSplitMax = 64;   // attention splits per (row, kv head) in decode
 constexpr int kLogitRows = 64;  // rows of the logits staging buffer (prefill ALL)
+constexpr int kSplitRows = 1024;  // rows of one many-row LM head launch
 constexpr int kMaxStepWG = 1024; // upper bound on persistent decode-step workgroups
 
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
@@ -46,7 +47,7 @@ struct Layout {
   std::vector<size_t> wqkvQ, woQ, wguQ, wdownTQ;
   size_t lm_headQ;
   size_t final_norm, rope, kv, page_table, pos, pending, slot, hist, ll, ll_words, layer_tab, trace;
-  size_t row_stream, row_pos, feed, items, x, h, q, qM, o32, oM, m32, mM, part, logits, gemm_ws, gemm_ws_bytes, scratch_u32;
+  size_t row_stream, row_pos, feed, items, x, h, q, qM, o32, oM, m32, mM, part, logits, gemm_ws, gemm_ws_bytes, scratch_u32, split, row_scale;
   // RowNorm buffers of the lockstep decode rows: column-block counters (zero
   // between launches; in the zero-initialised range) and row sums of squares.
   size_t nrm_cnt, nrm_ss;
@@ -209,6 +210,10 @@ Layout make_layout(const hh_config& c) {
   L.gemm_ws_bytes = std::min<size_t>((size_t)4 * R * std::max((size_t)2 * F, (size_t)L.nqkv) * 4, (size_t)256 << 20);
   L.gemm_ws = take(L.gemm_ws_bytes);
   L.scratch_u32 = take(256);
+  // Many-row LM head: the normalised rows as two fp16 terms, and their scales.
+  const size_t sr = bf ? (std::min<size_t>(R, kSplitRows) + 15) / 16 * 16 : 0;
+  L.split = take(2 * sr * d * 2);
+  L.row_scale = take(sr * 4);
   L.nrm_ss = take((size_t)32 * (d / 64) * 4);
   L.total = off;
   return L;
@@ -266,6 +271,16 @@ struct hh_ctx {
     return HH_ERR_HIP;
   }
 };
+
+// Device memory of the context's own GPU (kernels may write it).
+static bool on_this_device(const hh_ctx* c, const void* p) {
+  hipPointerAttribute_t a;
+  if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == c->device;
+}
 
 #define HIPCHK(ctx, expr)                                      \
   do {                                                         \
@@ -590,6 +605,32 @@ void enqueue_head_row(hh_ctx* c, int row, float* logits, unsigned long long* slo
                 g.vocab, row, c->at<int>(L.row_stream), logits, slot);
 }
 
+// LM head of rows [r0, r0 + n) of x into logits (n x vocab, device memory);
+// with slot, the last of them also gives its stream's greedy key.
+template <typename TW, typename TKV, typename TM>
+void enqueue_head_rows(hh_ctx* c, int r0, int n, float* logits, unsigned long long* slot) {
+  const Layout& L = c->L;
+  const hh_config& g = c->cfg;
+  using DK = DecodeKernels<TW, TKV, TM>;
+  using GK = GemmKernels<TM, TKV>;
+  const int d = g.d_model;
+  float* x = c->at<float>(L.x) + (size_t)r0 * d;
+  const int* rs = c->at<int>(L.row_stream) + r0;
+  const float* fn = c->at<float>(L.final_norm);
+  if (sizeof(TM) == 2 && g.weight_format == HH_WF_DTYPE) {
+    GK::logits_split(c->stream, x, n, fn, g.rms_eps, c->at<_Float16>(L.split), c->at<float>(L.row_scale),
+                     c->at<TM>(L.lm_headM), d, g.vocab, 1.f / c->wscale, logits, slot, rs, n - 1);
+    return;
+  }
+  // fp32 models, and 4-bit ones, whose head takes fp16 rows.
+  TM* h = c->at<TM>(L.h);
+  if (GK::norm_fusable(d)) GK::rmsnorm(c->stream, n, x, d, fn, g.rms_eps, h);
+  else DK::rmsnorm_rows(c->stream, n, x, fn, g.rms_eps, d, h);
+  const GemmWorkspace gws{c->at<float>(L.gemm_ws), L.gemm_ws_bytes};
+  GK::logits(c->stream, gws, h, n, c->at<TM>(L.lm_headM), d, g.vocab, 1.f / c->wscale, logits, slot, rs,
+             L.wqkvT16.empty() ? nullptr : c->at<TM>(L.lm_headT16), RowNorm(), n - 1);
+}
+
 template <typename TW, typename TKV, typename TM>
 hh_status do_prefill(hh_ctx* c, int s, const int32_t* tokens, int n, int mode, float* logits, int32_t* next) {
   const Layout& L = c->L;
@@ -612,12 +653,17 @@ hh_status do_prefill(hh_ctx* c, int s, const int32_t* tokens, int n, int mode, f
     enqueue_layers<TW, TKV, TM>(c, P, false, 1, -2, nullptr, s, c->len[s] + r0);
     unsigned long long* slot = c->at<unsigned long long>(L.slot);
     if (mode == HH_LOGITS_ALL) {
-      for (int b0 = 0; b0 < P; b0 += kLogitRows) {
-        const int nb = std::min(kLogitRows, P - b0);
-        for (int i = 0; i < nb; ++i)
-          enqueue_head_row<TW, TKV, TM>(c, b0 + i, lbuf + (size_t)i * V, (last && b0 + i == P - 1) ? slot : nullptr);
-        HIPCHK(c, hipMemcpyAsync(logits + (size_t)(r0 + b0) * V, lbuf, (size_t)nb * V * sizeof(float),
-                                 hipMemcpyDefault, st));
+      // Device memory of this GPU is written directly, anything else through
+      // the staging rows.
+      const bool direct = on_this_device(c, logits);
+      const int most = direct ? kSplitRows : std::min(L.logit_rows, kSplitRows);
+      for (int b0 = 0; b0 < P; b0 += most) {
+        const int nb = std::min(most, P - b0);
+        float* dst = direct ? logits + (size_t)(r0 + b0) * V : lbuf;
+        enqueue_head_rows<TW, TKV, TM>(c, b0, nb, dst, (last && b0 + nb == P) ? slot : nullptr);
+        if (!direct)
+          HIPCHK(c, hipMemcpyAsync(logits + (size_t)(r0 + b0) * V, lbuf, (size_t)nb * V * sizeof(float),
+                                   hipMemcpyDefault, st));
       }
     } else if (last) {
       enqueue_head_row<TW, TKV, TM>(c, P - 1, mode == HH_LOGITS_LAST ? lbuf : nullptr, slot);

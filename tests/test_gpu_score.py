@@ -1,0 +1,52 @@
+"""GPU tests of the many-row LM head (HH_LOGITS_ALL): on a model without
+layers the logits are RMSNorm(E[token]) . E^T, so the head stands alone
+against fp64, at the precision of 32-bit inputs."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_util import new_context
+from paper_2606_12154_amd import hh
+
+pytestmark = pytest.mark.gpu
+
+
+def reference(shape, tensors, toks):
+    w = synth.weights_as_f64(shape, tensors)
+    x = w["embed"][toks]
+    h = x / np.sqrt((x * x).mean(-1, keepdims=True) + shape.rms_eps) * w["final_norm"]
+    return h @ w["embed"].T, np.abs(h) @ np.abs(w["embed"]).T
+
+
+# Widths that end inside a group of 64 columns, with and without 16-byte rows;
+# rows at the edges of the 16-row blocks, the tiles and the launches of 1,024.
+@pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
+@pytest.mark.parametrize("vocab,n", [(1000, 1), (1003, 15), (1000, 16), (1003, 17), (700, 64), (700, 65), (530, 130),
+                                     (257, 1030)])
+def test_head_alone(dtype, vocab, n):
+    import torch
+    shape = synth.ModelShape(0, 512, 4, 2, 64, 64, vocab, 1e-5, 1e4, True, dtype)
+    tensors = synth.make_weights(shape, 31, gain_std=0.5)
+    toks = synth.make_tokens(vocab, n, 32)
+    ref, size = reference(shape, tensors, toks)
+    # The split keeps 22 bits of a row's largest value (at most 16 times its
+    # rms here) and sums are 32-bit: 2^-17 of the sum of magnitudes leaves room
+    # for both, and is 64 times below what plain fp16 rows can err by.
+    tol = 2.0 ** -17 * size
+    ctx = new_context(shape, tensors, streams=1, context=n + 4)
+    try:
+        # One float past a 16-byte boundary, with guards on both sides.
+        buf = torch.full((n * vocab + 8,), 7.0, dtype=torch.float32, device="cuda")
+        out = buf[1:1 + n * vocab]
+        nxt = np.zeros(1, dtype=np.int32)
+        torch.cuda.synchronize()
+        hh.hh_prefill(ctx.ctx, 0, toks, hh.HH_LOGITS_ALL, out.data_ptr(), nxt.ctypes.data)
+        got = out.cpu().numpy().reshape(n, vocab)
+        assert float(buf[0]) == 7.0 and bool((buf[1 + n * vocab:] == 7.0).all())
+        assert (np.abs(got - ref) <= tol).all(), float((np.abs(got - ref) / size).max())
+        assert int(nxt[0]) == int(np.argmax(got[-1]))
+        ctx.reset()
+        nxt2, host = ctx.prefill(0, toks, logits="all")  # through the staging rows
+        assert nxt2 == int(nxt[0]) and (np.abs(host - ref) <= tol).all()
+    finally:
+        ctx.close()
