@@ -884,6 +884,136 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
   wait_stages<T::NI>(0);  // no direct-to-LDS load outlives the workgroup
 }
 
+// ---------------------------------------------------------------- mid kernel (at most 128 rows)
+
+// Short prompts and lockstep decoding past 32 streams: C[M <= 128, N] = A W^T is
+// bound by bringing operands into the CUs, so a workgroup owns 64 logical
+// columns over one K range and takes each operand in once, through a ring of
+// DEPTH 64-wide K steps in LDS with DEPTH - 2 of them in flight (direct loads of
+// whole 128-byte lines; the 16-row pattern of an MFMA operand loaded straight
+// to registers reaches a quarter of their rate: 38 against 150 GB/s a CU from
+// the L2).  The small-tile kernel, which has two steps in flight and reads
+// the weights once per 64 rows, is slower where launch_mid says so (gate/up at
+// 64 rows 24.1 -> 18.1 us; what is left there is ~5 us of start and end, and
+// 0.4 us a step at ~13 TB/s into the CUs).
+// Eight waves: wave w has columns 16 (w % 4) .. + 16 and the 32-wide half w / 4
+// of each step, for all MT * 16 rows; the halves are added in LDS.
+template <int MT_>
+struct Mid {
+  static constexpr int MT = MT_, ROWS = 16 * MT, STAGE = (ROWS + 64) * 128, DEPTH = MT == 8 ? 6 : 8;
+  static constexpr int XI = MT == 8 ? 2 : 1, NI = XI + 1;  // a wave's loads per step
+  static constexpr int LDS = DEPTH * STAGE, LDC = 68;
+  static_assert(ROWS * LDC * 4 <= LDS && LDS <= 160 * 1024, "ring, and the finished tile in it");
+};
+
+template <int MT, class Epi>
+__global__ __launch_bounds__(512, 2) void k_gemm_mid(const _Float16* __restrict__ A, int M,
+                                                     const _Float16* __restrict__ W, int K, int nb,
+                                                     int steps_per_split, float* __restrict__ partial, int ncols,
+                                                     Epi epi) {
+  using T = Mid<MT>;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  typedef __attribute__((address_space(3))) const f16x8 lds_f16x8;
+  const int cbk = blockIdx.x % nb, split = blockIdx.x / nb, n0 = cbk * 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int cw = wave & 3, kh = wave >> 2, l15 = lane & 15, h = lane >> 4;
+  const int s0 = split * steps_per_split, nk = min(K / 64, s0 + steps_per_split) - s0;
+  const unsigned rowb = (unsigned)K * 2;
+
+  // Activations: wave w's instruction q fills row group w + 8 q (8 rows, 1 KiB;
+  // with 32 rows waves 4 .. 7 repeat waves 0 .. 3).  Groups past M load the first
+  // rows again, rows past M in a group are outside the buffer's range; no
+  // such row is stored.  Weights: wave w fills row group w of the 64 columns.
+  const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(reinterpret_cast<const char*>(A) + (size_t)s0 * 128), (short)0, (int)((unsigned)M * rowb - (unsigned)s0 * 128),
+      0x00020000);
+  const int b0 = epi.b_row(n0), br = epi.b_row(n0 + 8 * wave);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(reinterpret_cast<const char*>(W) + ((size_t)b0 * K + (size_t)s0 * 64) * 2), (short)0, -1, 0x00020000);
+  const int xw = MT == 2 ? wave & 3 : wave;
+  const int va = (lane >> 3) * (int)rowb + 16 * ((lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7));
+  unsigned oa[T::XI];
+#pragma unroll
+  for (int q = 0; q < T::XI; ++q) oa[q] = 8 * (xw + 8 * q) < M ? (unsigned)(8 * (xw + 8 * q)) * rowb : 0u;
+  const unsigned ow = br < 0 ? 0u : (unsigned)(br - b0) * rowb;
+  // Steps past the range load its last one again, into slots nobody reads.
+  auto issue = [&](int s, unsigned so) {
+    const unsigned koff = (unsigned)min(s, nk - 1) * 128;
+    lds_char* dst = (lds_char*)smem + so;
+#pragma unroll
+    for (int q = 0; q < T::XI; ++q) buffer_lds16(ra, dst + (xw + 8 * q) * 1024, va, oa[q] + koff);
+    buffer_lds16(rw, dst + T::ROWS * 128 + wave * 1024, va, ow + koff);
+  };
+  f32x4 acc[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int fx = l15 * 128 + 16 * ((4 * kh + h) ^ (l15 >> 1)), fw = fx + (T::ROWS + 16 * cw) * 128;
+  f16x8 x[2][MT], w[2];
+  auto frags = [&](int set, unsigned so) {
+    const lds_char* base = (const lds_char*)smem + so;
+    w[set] = *(lds_f16x8*)(base + fw);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) x[set][m] = *(lds_f16x8*)(base + fx + m * 2048);
+  };
+#define HH_MID_WAIT(steps)                                                                            \
+  __builtin_amdgcn_s_waitcnt(((T::NI * (steps)) & 15) | (0x7 << 4) | (0xF << 8) | (((T::NI * (steps)) >> 4) << 14))
+#pragma unroll
+  for (int s = 0; s + 1 < T::DEPTH; ++s) issue(s, s * T::STAGE);
+  HH_MID_WAIT(T::DEPTH - 2);
+  bare_barrier();
+  frags(0, 0);
+  unsigned so = 0, sp = (T::DEPTH - 1) * T::STAGE;  // this step's slot and the one before it
+  // Step s + 1 has landed (this wave's loads, then every wave's), and every
+  // wave is done with step s - 1, whose slot is refilled.  The next step's
+  // fragments are read under this one's products.
+  auto step = [&](int s, int set) {
+    HH_MID_WAIT(T::DEPTH - 3);
+    bare_barrier();
+    issue(s + T::DEPTH - 1, sp);
+    const unsigned sn = so + T::STAGE == T::LDS ? 0u : so + T::STAGE;
+    frags(set ^ 1, sn);
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w[set], x[set][m], acc[m], 0, 0, 0);
+#pragma unroll
+    for (int m = 0; m < MT + 1; ++m) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    sp = so;
+    so = sn;
+  };
+  int s = 0;
+  for (; s + 1 < nk; s += 2) {
+    step(s, 0);
+    step(s + 1, 1);
+  }
+  if (s < nk) step(s, 0);
+#undef HH_MID_WAIT
+  __builtin_amdgcn_s_waitcnt(0);  // no direct-to-LDS load is left
+  __syncthreads();
+  float* Cs = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    if (kh == g) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        f32x4* c = reinterpret_cast<f32x4*>(Cs + (16 * m + l15) * T::LDC + 16 * cw + 4 * h);
+        *c = g ? *c + acc[m] : acc[m];
+      }
+    }
+    __syncthreads();
+  }
+  if (partial) {  // ncols % 64 == 0
+    float* dst = partial + (size_t)split * M * ncols + n0;
+    for (int i = threadIdx.x; i < M * 16; i += 512)
+      *reinterpret_cast<f32x4*>(dst + (size_t)(i >> 4) * ncols + 4 * (i & 15)) =
+          *reinterpret_cast<const f32x4*>(Cs + (i >> 4) * T::LDC + 4 * (i & 15));
+    return;
+  }
+  epi(Cs, T::LDC, 0, M, n0, T::ROWS, 64);
+}
+
 // ---------------------------------------------------------------- launchers
 
 // Launchers return the number of K splits used.  With defer set, split
@@ -941,6 +1071,53 @@ static int launch_tile(hipStream_t st, GemmWorkspace ws, const _Float16* A, int 
     k_splitk_finalize<Epi><<<((M + kFinRows - 1) / kFinRows) * nf, 256, 0, st>>>(part, splits, M, n_cols, nf, e);
   }
   return splits;
+}
+
+// Returns the K splits, 0 where the small-tile kernel is the better one.  us a
+// layer of the 1B model, this kernel / small tiles: gate/up at 24 rows 17.8 /
+// 20.3, 40 rows 17.5 / 22.2, 64 rows 18.1 / 24.1, 99 rows 21.9 / 25.0, 128 rows
+// 23.6 / 25.4; O and down together at 24 rows 14.4 / 13.7, 40 rows 15.2 / 16.1,
+// 64 rows 16.6 / 17.8, 99 rows 21.6 / 19.4; QKV at 24 rows 6.2 / 5.8, 40 rows
+// 6.7 / 7.0, 64 rows 7.4 / 8.0, 99 rows 9.6 / 9.6; the LM head at 64 rows 145 /
+// 115.  So: gate/up at any of these row counts, O, down and QKV from 33 to 64.
+template <int MT, class Epi>
+static int launch_mid(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* W, int K, int n_cols,
+                      const Epi& e, bool defer) {
+  using T = Mid<MT>;
+  const int nb = (n_cols + 63) / 64, nk = K / 64;
+  int splits = std::max(1, std::min((256 + nb / 2) / nb, nk / 4));
+  while (splits > 1 && (size_t)splits * M * n_cols * sizeof(float) > ws.bytes) --splits;
+  const int per = (nk + splits - 1) / splits;
+  splits = (nk + per - 1) / per;
+  if (nb * splits < 64) return 0;  // a quarter of the CUs
+  static bool attr = false;
+  if (!attr) {
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_mid<MT, Epi>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
+    attr = true;
+  }
+  float* part = splits > 1 ? ws.ptr : nullptr;
+  k_gemm_mid<MT, Epi><<<nb * splits, 512, T::LDS, st>>>(A, M, W, K, nb, per, part, n_cols, e);
+  if (splits > 1 && !defer) {
+    const int nf = (n_cols + 127) / 128;
+    k_splitk_finalize<Epi><<<((M + kFinRows - 1) / kFinRows) * nf, 256, 0, st>>>(part, splits, M, n_cols, nf, e);
+  }
+  return splits;
+}
+
+template <class Epi>
+static int run_mid(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* W, int K, int n_cols,
+                   const Epi& e, GemmKind kind, bool defer) {
+  if constexpr (std::is_same<Epi, EpiLogits<false>>::value) {
+    return 0;
+  } else {
+    if (M > 128 || n_cols % 64) return 0;
+    if (M > 32 && M <= 64) return launch_mid<4>(st, ws, A, M, W, K, n_cols, e, defer);
+    if constexpr (std::is_same<Epi, EpiGateUp<_Float16>>::value)
+      return M <= 32 ? launch_mid<2>(st, ws, A, M, W, K, n_cols, e, defer)
+                     : launch_mid<8>(st, ws, A, M, W, K, n_cols, e, defer);
+    return 0;
+  }
 }
 
 // ---------------------------------------------------------------- skinny kernel (<= 32 rows)
@@ -1550,6 +1727,8 @@ static int run_gemm(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const 
     if (K % 64 == 0) {
       const _Float16* Ah = reinterpret_cast<const _Float16*>(A);
       const _Float16* Wh = reinterpret_cast<const _Float16*>(W);
+      const int spm = run_mid(st, ws, Ah, M, Wh, K, n_cols, e, kind, defer);
+      if (spm > 0) return spm;
       const int sp = run_tile(st, ws, Ah, M, Wh, K, n_cols, e, kind, defer);
       if (sp > 0) return sp;
       const long long ntn = (n_cols + 127) / 128;
