@@ -83,19 +83,27 @@ struct RowNorm {
   float* ss_out = nullptr;
 };
 
+// A matrix laid out for the <= 32-row GEMMs: fp16 operand tiles (tile16), and
+// for 4-bit models the codes themselves (tile_q4).  Null: not kept.
+struct WTiles {
+  const _Float16* h = nullptr;
+  const unsigned char* q = nullptr;  // codes: 1 KiB per 16 rows x 128 k
+  const _Float16* s = nullptr;       // scales (times 2^s), see tile_q4
+  bool by_k = false;                 // scales belong to k (W_down), not to rows
+};
+
 template <typename TM, typename TKV>
 struct GemmKernels {
-  // Wt (optional): the same matrix as 16 x 32 operand tiles (tile16), used
-  // for M <= 32 rows.
+  // Wt (optional): the same matrix's tiles, used for M <= 32 rows.
   static void qkv(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int hq, int hkv, float scale,
                   const int* row_stream, const int* row_pos, const float2* rope, float* q, TM* qM, TKV* kv,
-                  KvLayout L, int layer, const int* page_table, const TM* Wt = nullptr);
+                  KvLayout L, int layer, const int* page_table, const WTiles& Wt = WTiles());
   // The same product for lockstep decode rows with the split-K reduction
   // left to the attention kernel: returns the K splits (partials in ws.ptr
   // when > 1, nothing written yet); 1: the epilogue ran as in qkv().
   static int qkv_deferred(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int hq, int hkv,
                           float scale, const int* row_stream, const int* row_pos, const float2* rope, float* q, TKV* kv,
-                          KvLayout L, int layer, const int* page_table, const TM* Wt = nullptr,
+                          KvLayout L, int layer, const int* page_table, const WTiles& Wt = WTiles(),
                           const RowNorm& rn = RowNorm());
   // x += A W^T * scale; with gain, then h = rmsnorm(x) * gain (fused into the
   // split-K reduction when K is split).  Requires norm_fusable(N) with gain.
@@ -104,7 +112,7 @@ struct GemmKernels {
   // returns true then, and the product reading h takes
   // RowNorm{ss, N / 64, N, eps}.
   static bool resid(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int K, int N, float scale, float* x,
-                    const float* gain = nullptr, float eps = 0.f, TM* h = nullptr, const TM* Wt = nullptr,
+                    const float* gain = nullptr, float eps = 0.f, TM* h = nullptr, const WTiles& Wt = WTiles(),
                     float* ss = nullptr, int* cnt = nullptr, int ncnt = 0);
   static bool norm_fusable(int N);
   // h = rmsnorm(x) * gain, one row per workgroup (norm_fusable(N)); with
@@ -112,9 +120,9 @@ struct GemmKernels {
   static void rmsnorm(hipStream_t st, int M, float* x, int N, const float* gain, float eps, TM* h,
                       const int* rows = nullptr);
   static void gateup(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int F, float scale, TM* m,
-                     const TM* Wt = nullptr, const RowNorm& rn = RowNorm());
+                     const WTiles& Wt = WTiles(), const RowNorm& rn = RowNorm());
   static void logits(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int V, float scale, float* logits,
-                     unsigned long long* slot, const int* row_stream, const TM* Wt = nullptr,
+                     unsigned long long* slot, const int* row_stream, const WTiles& Wt = WTiles(),
                      const RowNorm& rn = RowNorm(), int slot_row = -1);
   // Final norm and LM head of M rows of x on fp16 operands at the precision
   // of 32-bit inputs (16-bit TM only): split holds 32 ceil(M / 16) rows of d
@@ -230,6 +238,18 @@ void q4g32(hipStream_t st, const __bf16* src, size_t rows, int K, unsigned char*
 // 16 x 32 operand tiles of a [rows][K] fp16 matrix taken as logical_rows rows
 // (see k_tile16); dst holds ceil(logical_rows / 16) * 16 * K elements.
 void tile16(hipStream_t st, const _Float16* src, _Float16* dst, int rows, int K, int logical_rows, int interleave_f);
+// The stored 4-bit rows of a matrix (K / 2 + K / 16 bytes each) as operand
+// tiles of logical_rows rows (interleave_f as in tile16), K % 128 == 0:
+// codes: chunk (rb (K / 128) + b) 64 + l (16 bytes) holds row 16 rb + l % 16,
+// k 128 b + 32 j + 8 (l / 16) .. + 8 in dword j, element 2 p in nibble p and
+// 2 p + 1 in nibble p + 4; rows past the matrix hold zeros (code 8);
+// scales: 4 halfs (s * scale) of the row's groups 4 b .. + 4 at index
+// ((rb (K / 128) + b) 16 + row % 16) 4.
+// by_k: src holds the rows of the transpose (K of them, rows / 2 + rows / 16
+// bytes, groups along the logical rows, a multiple of 32): the scale of (row n,
+// k) is at index (n / 32) K + k.
+void tile_q4(hipStream_t st, const unsigned char* src, unsigned char* codes, _Float16* scales, int rows, int K,
+             int logical_rows, int interleave_f, bool by_k, float scale);
 // dst = src^T for a row-major rows x cols matrix.
 template <typename T>
 void transpose(hipStream_t st, const T* src, T* dst, int rows, int cols);

@@ -346,6 +346,35 @@ struct EpiLogits {
       }
     }
   }
+  // One 32 x 64 block of a workgroup of 512 threads that walks column blocks:
+  // thread t takes four columns of row t / 16 and keeps the best key it has
+  // seen; finish() gives each row's to its slot, one atomic per workgroup
+  // and row (2,004 blocks' atomics on the same few words were half of the
+  // 4-bit head's time at 6 rows).
+  __device__ void block(const float* Cs, int ldc, int M, int n0, unsigned long long& best) const {
+    const int row = threadIdx.x >> 4, col = n0 + 4 * (threadIdx.x & 15);
+    if (row >= M) return;
+    const f32x4 c = *reinterpret_cast<const f32x4*>(Cs + row * ldc + col - n0);
+    float* dst = logits ? logits + (size_t)row * V + col : nullptr;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (col + e >= V) continue;
+      const float v = c[e] * scale;
+      if (dst) dst[e] = v;
+      const unsigned long long k = argmax_key(v, (uint32_t)(col + e));
+      best = k > best ? k : best;
+    }
+  }
+  __device__ void finish(int M, unsigned long long best) const {
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+      const unsigned long long k = __shfl_xor(best, o);
+      best = k > best ? k : best;
+    }
+    const int row = threadIdx.x >> 4;
+    if (slot && (threadIdx.x & 15) == 0 && row < M && (slot_row < 0 || row == slot_row))
+      atomicMax(slot + row_stream[row], best);
+  }
   __device__ void operator()(const float* Cs, int ldc, int m0, int M, int n0, int BM, int BN) const {
     if (logits)
       for (int idx = threadIdx.x; idx < BM * BN; idx += blockDim.x) {
@@ -1149,17 +1178,11 @@ __device__ __forceinline__ void row_norm_loads(float4& ssv, const RowNorm& rn, i
 }
 
 // acc0[j] of lane l: column 16 rw + 4 (l / 16) + j, row l % 16 (acc1: row
-// + 16).  K groups add into the LDS tile Cs (32 x 68 floats, which the caller's
-// activation buffer holds once every wave is done with it) in group order;
-// rows are scaled by their norm factors (RowNorm consumer), then the tile
-// goes to the split partials or through the epilogue.  A RowNorm producer's
-// last split of the column block then finishes the residual (rs, flag: LDS
-// scratch of 32 floats and one int).
-template <class Epi, int KW>
-__device__ __forceinline__ void skinny_tail(float* Cs, const f32x4& acc0, const f32x4& acc1, int rw, int kg, int lane,
-                                            float* __restrict__ partial, int split, int splits, int cb, int M,
-                                            int ncols, int n0, const Epi& epi, const RowNorm& rn,
-                                            const float4& ssv, float* rs, int* flag) {
+// + 16).  K groups add into the LDS tile Cs (32 x 68 floats) in group order;
+// rows are scaled by their norm factors (RowNorm consumer; rs: 32 floats of LDS).
+template <int KW>
+__device__ __forceinline__ void skinny_tile(float* Cs, const f32x4& acc0, const f32x4& acc1, int rw, int kg, int lane,
+                                            const RowNorm& rn, const float4& ssv, float* rs) {
   constexpr int LDC = 68;
   const int col = 16 * rw + 4 * (lane >> 4), r = lane & 15;
   float f0 = 1.f, f1 = 1.f;  // norm factors of rows r and r + 16
@@ -1186,6 +1209,19 @@ __device__ __forceinline__ void skinny_tail(float* Cs, const f32x4& acc0, const 
     }
     __syncthreads();
   }
+}
+
+// The finished tile (Cs: the caller's activation buffer, once every wave is done
+// with it) goes to the split partials or through the epilogue.  A RowNorm
+// producer's last split of the column block then finishes the residual (flag:
+// LDS scratch of one int).
+template <class Epi, int KW>
+__device__ __forceinline__ void skinny_tail(float* Cs, const f32x4& acc0, const f32x4& acc1, int rw, int kg, int lane,
+                                            float* __restrict__ partial, int split, int splits, int cb, int M,
+                                            int ncols, int n0, const Epi& epi, const RowNorm& rn,
+                                            const float4& ssv, float* rs, int* flag) {
+  constexpr int LDC = 68;
+  skinny_tile<KW>(Cs, acc0, acc1, rw, kg, lane, rn, ssv, rs);
   if (partial) {
     bool producer = false;
     if constexpr (std::is_same<Epi, EpiResid>::value) producer = rn.cnt != nullptr;
@@ -1574,12 +1610,246 @@ static bool launch_skinny_res(hipStream_t st, const _Float16* A, int M, const _F
   }
 }
 
+// ---------------------------------------------------------------- skinny kernel on 4-bit codes
+
+// The activation-resident product on a 4-bit model's stored codes: lockstep
+// decoding streamed the fp16 copies of the dequantized values, 3.6 times the
+// bytes.  A lane's 16-byte load holds its operand rows' codes of four K
+// blocks; a block's eight codes become fp16 values of exactly q (nibbles in the
+// mantissa of 1024, then minus 1032) times the group's scale, the same fp16
+// operand as the copy's.  us at 6 rows of the 1B model, fp16 tiles / codes: gate/up
+// 14.5 / 8.8, down 11.4 / 9.0, O 7.2 / 7.1, QKV 5.0 / 4.6, LM head 86 / 35; what is
+// left is a launch's start and end and the activations' round trip, and in
+// the head the unpacking (15 instructions per 8 codes and lane).
+// Waves, K groups, activations and the tail are k_gemm_skinny_res's.  BY_K:
+// scales belong to k (W_down, grouped along its output rows) and go through
+// LDS.  LOOP (LM head): a workgroup walks the column blocks with its
+// activations resident and the next block's codes in flight.
+// mask and magic: 0x000F000F and 0x64006400, in registers (q4_constants), so that
+// each pair takes one and-or instruction, which has no room for literals.
+__device__ __forceinline__ void q4_constants(unsigned& mask, unsigned& magic) {
+  asm("s_mov_b32 %0, 0x000f000f" : "=s"(mask));
+  asm("v_mov_b32 %0, 0x64006400" : "=v"(magic));
+}
+__device__ __forceinline__ f16x8 q4_values(unsigned w, unsigned mask, unsigned magic) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  const h2 off = {(_Float16)1032.f, (_Float16)1032.f};
+  f16x8 r;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const unsigned t = ((w >> (4 * p)) & mask) | magic;
+    const h2 v = __builtin_bit_cast(h2, t) - off;
+    r[2 * p] = v[0];
+    r[2 * p + 1] = v[1];
+  }
+  return r;
+}
+
+constexpr int q4_pitch(int nb4) { return 128 * nb4 + 8; }  // LDS row of a K group's activations (halfs)
+
+template <class Epi, int NB4, int KW, bool BY_K, bool LOOP, bool TWO>
+__global__ __launch_bounds__(256 * KW) void k_gemm_skinny_q4(const _Float16* __restrict__ A, int M, WTiles wt, int K,
+                                                             int nb, int blocks_per_split,
+                                                             float* __restrict__ partial, int ncols, Epi epi,
+                                                             RowNorm rn) {
+  constexpr int XQ = (16 * NB4 + 63) / 64, PITCH = q4_pitch(NB4);
+  constexpr unsigned kOob = 0x80000000u;  // past every buffer range here
+  constexpr int kNt = 2;                  // codes are read once per step: streaming policy
+  extern __shared__ __attribute__((aligned(16))) _Float16 xsd[];
+  __shared__ float rs[32];
+  __shared__ int flag;
+  float4 ssv = make_float4(0.f, 0.f, 0.f, 0.f);
+  row_norm_loads(ssv, rn, M);
+  int cb = blockIdx.x % nb;
+  const int split = LOOP ? 0 : blockIdx.x / nb;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int rw = wave & 3, kg = wave >> 2;
+  const int kb0 = split * blocks_per_split;  // 128-wide K blocks
+  const int n_all = min(K / 128 - kb0, blocks_per_split);
+  const int lo = (n_all * kg) / KW, n4 = (n_all * (kg + 1)) / KW - lo;  // this K group's, at most NB4
+  const int kbase = 128 * (kb0 + lo), nk4 = K / 128;
+  _Float16* xs = xsd + (size_t)kg * 32 * PITCH;
+  _Float16* after = xsd + (size_t)KW * 32 * PITCH;
+  _Float16* sk = after + (size_t)kg * 2 * 128 * NB4;  // BY_K: scales of the two 32-column groups
+  float* tail = reinterpret_cast<float*>(LOOP ? after : xsd);
+
+  const size_t rb16 = (size_t)((ncols + 15) / 16);
+  const __amdgpu_buffer_rsrc_t xres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)A, (short)0, (int)((size_t)M * K * 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t cres =
+      __builtin_amdgcn_make_buffer_rsrc((void*)wt.q, (short)0, (int)(rb16 * 16 * K / 2), 0x00020000);
+  const __amdgpu_buffer_rsrc_t sres = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)wt.s, (short)0, (int)(BY_K ? (size_t)(ncols / 32) * K * 2 : rb16 * 16 * (K / 32) * 2), 0x00020000);
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  u32x4 w[NB4], wn[LOOP ? NB4 : 1];
+  u32x2 sc[NB4], sn[LOOP ? NB4 : 1];
+  auto load = [&](u32x4* cw, u32x2* cs, int c) {
+    const unsigned b0 = (unsigned)((4 * c + rw) * nk4 + kb0 + lo);
+#pragma unroll
+    for (int u = 0; u < NB4; ++u) {
+      const bool ok = u < n4 && c < nb;
+      cw[u] = __builtin_bit_cast(
+          u32x4, __builtin_amdgcn_raw_buffer_load_b128(cres, ok ? ((b0 + u) * 64 + lane) * 16 : kOob, 0, kNt));
+      if (!BY_K)
+        cs[u] = __builtin_bit_cast(
+            u32x2, __builtin_amdgcn_raw_buffer_load_b64(sres, ok ? ((b0 + u) * 16 + (lane & 15)) * 8 : kOob, 0, kNt));
+    }
+  };
+  // Activations (rows past M and K past the group's read zeros, and a K
+  // group's missing blocks have zero scales: no branch below) and, with scales
+  // by k, the workgroup's scales first; then the codes.
+  static_assert(XQ * 64 == 16 * NB4, "whole waves of chunks");
+  f16x8 xv[8][XQ];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int q = 0; q < XQ; ++q) {
+      const int kc = lane + 64 * q;
+      xv[i][q] = __builtin_bit_cast(
+          f16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                     xres, kc < 16 * n4 ? (unsigned)(((rw + 4 * i) * K + kbase + 8 * kc) * 2) : kOob, 0, 0));
+    }
+  constexpr int SJ = (32 * NB4 + 255) / 256;
+  f16x8 sv[BY_K ? SJ : 1];
+  if constexpr (BY_K) {
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) {
+      const int c = (threadIdx.x & 255) + 256 * j, g = c / (16 * NB4), kc = c % (16 * NB4);
+      sv[j] = __builtin_bit_cast(
+          f16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                     sres, g < 2 && kc < 16 * n4 ? (unsigned)(((2 * cb + g) * K + kbase + 8 * kc) * 2) : kOob, 0, 0));
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  load(w, sc, cb);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int q = 0; q < XQ; ++q) {
+      const int kc = lane + 64 * q;
+      *reinterpret_cast<f16x8*>(xs + (rw + 4 * i) * PITCH + 8 * kc) = xv[i][q];
+    }
+  if constexpr (BY_K) {
+#pragma unroll
+    for (int j = 0; j < SJ; ++j) {
+      const int c = (threadIdx.x & 255) + 256 * j, g = c / (16 * NB4), kc = c % (16 * NB4);
+      if (g < 2) *reinterpret_cast<f16x8*>(sk + g * 128 * NB4 + 8 * kc) = sv[j];
+    }
+  }
+  __syncthreads();
+  const _Float16* xb = xs + (lane & 15) * PITCH + 8 * (lane >> 4);
+  const _Float16* sb = sk + (rw >> 1) * 128 * NB4 + 8 * (lane >> 4);
+  unsigned long long best = 0ull;
+  unsigned mask, magic;
+  q4_constants(mask, magic);
+  while (true) {
+    if constexpr (LOOP) load(wn, sn, cb + (int)gridDim.x);  // past the last block: zeros, no access
+    f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < NB4; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const _Float16* xp = xb + 128 * u + 32 * j;
+        const f16x8 x0 = *reinterpret_cast<const f16x8*>(xp);
+        f16x8 a = q4_values(w[u][j], mask, magic);
+        if constexpr (BY_K) {
+          a = a * *reinterpret_cast<const f16x8*>(sb + 128 * u + 32 * j);
+        } else {
+          const _Float16 f = __builtin_bit_cast(_Float16, (unsigned short)(sc[u][j >> 1] >> (16 * (j & 1))));
+          a = a * f16x8{f, f, f, f, f, f, f, f};
+        }
+        acc0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, x0, acc0, 0, 0, 0);
+        if constexpr (TWO)
+          acc1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, *reinterpret_cast<const f16x8*>(xp + 16 * PITCH), acc1, 0, 0, 0);
+      }
+    if (!LOOP) __syncthreads();  // every wave is done with the activations
+    if constexpr (!LOOP) {
+      skinny_tail<Epi, KW>(tail, acc0, acc1, rw, kg, lane, partial, split, (int)gridDim.x / nb, cb, M, ncols, cb * 64,
+                           epi, rn, ssv, rs, &flag);
+      break;
+    } else {
+      skinny_tile<KW>(tail, acc0, acc1, rw, kg, lane, rn, ssv, rs);
+      epi.block(tail, 68, M, cb * 64, best);
+    }
+    cb += gridDim.x;
+    if (cb >= nb) break;
+    __syncthreads();  // the tile is read out
+#pragma unroll
+    for (int u = 0; u < NB4; ++u) {
+      w[u] = wn[LOOP ? u : 0];
+      sc[u] = sn[LOOP ? u : 0];
+    }
+  }
+  if constexpr (LOOP) epi.finish(M, best);
+}
+
+template <class Epi, int NB4, int KW, bool BY_K, bool LOOP, bool TWO>
+static bool skinny_q4_run(hipStream_t st, int grid, const _Float16* A, int M, const WTiles& wt, int K, int nb, int per,
+                         float* part, int n_cols, const Epi& e, const RowNorm& rn) {
+  const size_t need = ((size_t)KW * 32 * q4_pitch(NB4) + (BY_K ? (size_t)KW * 2 * 128 * NB4 : 0)) * 2 +
+                      (LOOP ? kSkinnyTileBytes : 0);
+  constexpr size_t kLds = 159 * 1024;  // the kernel's static LDS takes the rest
+  if (need > kLds) return false;
+  static const hipError_t attr = [] {
+    const hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(k_gemm_skinny_q4<Epi, NB4, KW, BY_K, LOOP, TWO>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (r != hipSuccess) (void)hipGetLastError();  // the fp16 tiles are used instead
+    return r;
+  }();
+  if (attr != hipSuccess) return false;
+  k_gemm_skinny_q4<Epi, NB4, KW, BY_K, LOOP, TWO>
+      <<<grid, 256 * KW, std::max<size_t>(need, kSkinnyTileBytes), st>>>(A, M, wt, K, nb, per, part, n_cols, e, rn);
+  return true;
+}
+
+template <class Epi, int NB4, int KW, bool BY_K, bool LOOP>
+static bool skinny_q4_go(hipStream_t st, int grid, const _Float16* A, int M, const WTiles& wt, int K, int nb, int per,
+                         float* part, int n_cols, const Epi& e, const RowNorm& rn) {
+  return M > 16 ? skinny_q4_run<Epi, NB4, KW, BY_K, LOOP, true>(st, grid, A, M, wt, K, nb, per, part, n_cols, e, rn)
+                : skinny_q4_run<Epi, NB4, KW, BY_K, LOOP, false>(st, grid, A, M, wt, K, nb, per, part, n_cols, e, rn);
+}
+
+// Shapes: K a multiple of 128, at most 1,024 of it per K group, one workgroup
+// per (64 columns, split) up to two per CU, or the LM head, which loops.
+template <class Epi>
+static bool launch_skinny_q4(hipStream_t st, const _Float16* A, int M, const WTiles& wt, int K, int nb, int splits,
+                             int per32, float* part, int n_cols, int kw, const Epi& e, const RowNorm& rn) {
+  constexpr bool head = std::is_same<Epi, EpiLogits<false>>::value;
+  const int per = per32 / 4, g = (per + kw - 1) / kw;
+  if (!wt.q || K % 128 || per32 % 4 || g > 8) return false;
+  if ((size_t)((n_cols + 15) / 16) * 16 * K / 2 >= ((size_t)1 << 31) || (wt.by_k && n_cols % 64)) return false;
+  if constexpr (head) {
+    if (splits != 1 || kw != 2 || wt.by_k) return false;
+    return skinny_q4_go<Epi, 8, 2, false, true>(st, std::min(nb, 256), A, M, wt, K, nb, per, part, n_cols, e, rn);
+  } else {
+    if ((long long)nb * splits > 2 * 256) return false;
+    auto go = [&](auto n, auto k, auto by) {
+      return skinny_q4_go<Epi, decltype(n)::value, decltype(k)::value, decltype(by)::value, false>(
+          st, nb * splits, A, M, wt, K, nb, per, part, n_cols, e, rn);
+    };
+    using std::integral_constant;
+    using I1 = integral_constant<int, 1>;
+    using I2 = integral_constant<int, 2>;
+    using I4 = integral_constant<int, 4>;
+    using I8 = integral_constant<int, 8>;
+    using No = std::false_type;
+    if constexpr (std::is_same<Epi, EpiResid>::value) {
+      using Yes = std::true_type;
+      if (wt.by_k) return kw == 2 ? go(I8(), I2(), Yes()) : g <= 4 ? go(I4(), I1(), Yes()) : go(I8(), I1(), Yes());
+    }
+    if (wt.by_k) return false;
+    if (kw == 2) return g <= 4 ? go(I4(), I2(), No()) : go(I8(), I2(), No());
+    return g <= 4 ? go(I4(), I1(), No()) : go(I8(), I1(), No());
+  }
+}
+
 // Returns the K splits, 0 when the shape does not fit the 32-row kernels.
 // rn: see RowNorm; its producer half runs only in the activation-resident
 // kernel of a split residual product (*fused = 1 then, and the partials are
 // consumed in the kernel).
 template <class Epi>
-static int launch_skinny(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const _Float16* Wt, int K,
+static int launch_skinny(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, const WTiles& wt, int K,
                          int n_cols, const Epi& e, bool defer, RowNorm rn, int* fused) {
   if (fused) *fused = 0;
   // Buffer ranges take 31-bit byte offsets.
@@ -1594,14 +1864,17 @@ static int launch_skinny(hipStream_t st, GemmWorkspace ws, const _Float16* A, in
   // 8, which 4 slowed).
   int splits = std::max(1, std::min((256 + nb - 1) / nb, nk / 16));
   while (splits > 1 && (size_t)splits * M * n_cols * sizeof(float) > ws.bytes) --splits;
-  const int per = (nk + splits - 1) / splits;
+  int per = (nk + splits - 1) / splits;
+  if (wt.q) per = (per + 3) & ~3;  // whole 128-wide blocks of codes
   splits = (nk + per - 1) / per;
+  const _Float16* Wt = wt.h;
   float* part = splits > 1 ? ws.ptr : nullptr;
   if (!(std::is_same<Epi, EpiResid>::value && splits > 1 && n_cols % 64 == 0 && nb <= rn.ncnt)) rn.cnt = nullptr;
   // Unsplit (long) K ranges take two K groups per workgroup: eight waves per
   // CU keep more weight loads in flight (gate/up 17.0 -> 15.9 us at 32 rows).
   const int kw = splits == 1 ? 2 : 1;
-  if (!launch_skinny_res<Epi>(st, A, M, Wt, K, nb, splits, per, part, n_cols, kw, e, rn)) {
+  if (!launch_skinny_q4<Epi>(st, A, M, wt, K, nb, splits, per, part, n_cols, kw, e, rn) &&
+      !launch_skinny_res<Epi>(st, A, M, Wt, K, nb, splits, per, part, n_cols, kw, e, rn)) {
     rn.cnt = nullptr;
     if (kw == 2)
       k_gemm_skinny<Epi, 8, 2><<<nb * splits, 512, 0, st>>>(A, M, Wt, K, nb, per, part, n_cols, e, rn);
@@ -1713,13 +1986,12 @@ static int run_tile(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, 
 // scales A's rows first, and *fused says whether the producer half ran.
 template <typename TM, class Epi>
 static int run_gemm(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int K, int n_cols, const Epi& e,
-                    GemmKind kind, bool defer = false, const TM* Wt = nullptr, const RowNorm& rn = RowNorm(),
+                    GemmKind kind, bool defer = false, const WTiles& Wt = WTiles(), const RowNorm& rn = RowNorm(),
                     int* fused = nullptr) {
   if (fused) *fused = 0;
   if constexpr (sizeof(TM) == 2) {
-    if (M <= 32 && Wt && K % 64 == 0) {
-      const int sp = launch_skinny(st, ws, reinterpret_cast<const _Float16*>(A), M,
-                                   reinterpret_cast<const _Float16*>(Wt), K, n_cols, e, defer, rn, fused);
+    if (M <= 32 && Wt.h && K % 64 == 0) {
+      const int sp = launch_skinny(st, ws, reinterpret_cast<const _Float16*>(A), M, Wt, K, n_cols, e, defer, rn, fused);
       if (sp > 0) return sp;
     }
     if (rn.ss_in)
@@ -1821,7 +2093,7 @@ __global__ __launch_bounds__(256) void k_resid_norm(const float* __restrict__ pa
 template <typename TM, typename TKV>
 void GemmKernels<TM, TKV>::qkv(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int hq, int hkv, float scale,
                                const int* row_stream, const int* row_pos, const float2* rope, float* q, TM* qM,
-                               TKV* kv, KvLayout L, int layer, const int* page_table, const TM* Wt) {
+                               TKV* kv, KvLayout L, int layer, const int* page_table, const WTiles& Wt) {
   EpiQKV<TKV> e{hq, hkv, scale, row_stream, row_pos, rope, q, reinterpret_cast<TKV*>(qM), kv, L, layer, page_table};
   run_gemm<TM>(st, ws, A, M, W, d, (hq + 2 * hkv) * 64, e, GemmKind::QKV, false, Wt);
 }
@@ -1830,7 +2102,7 @@ template <typename TM, typename TKV>
 int GemmKernels<TM, TKV>::qkv_deferred(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int hq,
                                        int hkv, float scale, const int* row_stream, const int* row_pos,
                                        const float2* rope, float* q, TKV* kv, KvLayout L, int layer,
-                                       const int* page_table, const TM* Wt, const RowNorm& rn) {
+                                       const int* page_table, const WTiles& Wt, const RowNorm& rn) {
   EpiQKV<TKV> e{hq, hkv, scale, row_stream, row_pos, rope, q, nullptr, kv, L, layer, page_table};
   return run_gemm<TM>(st, ws, A, M, W, d, (hq + 2 * hkv) * 64, e, GemmKind::QKV, true, Wt, rn);
 }
@@ -1842,7 +2114,7 @@ bool GemmKernels<TM, TKV>::norm_fusable(int N) {
 
 template <typename TM, typename TKV>
 bool GemmKernels<TM, TKV>::resid(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int K, int N,
-                                 float scale, float* x, const float* gain, float eps, TM* h, const TM* Wt, float* ss,
+                                 float scale, float* x, const float* gain, float eps, TM* h, const WTiles& Wt, float* ss,
                                  int* cnt, int ncnt) {
   EpiResid e{N, scale, x};
   const bool norm = gain != nullptr;
@@ -1870,7 +2142,7 @@ void GemmKernels<TM, TKV>::rmsnorm(hipStream_t st, int M, float* x, int N, const
 
 template <typename TM, typename TKV>
 void GemmKernels<TM, TKV>::gateup(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int F, float scale,
-                                  TM* m, const TM* Wt, const RowNorm& rn) {
+                                  TM* m, const WTiles& Wt, const RowNorm& rn) {
   // Groups of 32 gate + 32 up columns: every tile width here is a multiple of 64.
   EpiGateUp<TM> e{F, 32, scale, m};
   run_gemm<TM>(st, ws, A, M, W, d, ((F + 31) / 32) * 64, e, GemmKind::GateUp, false, Wt, rn);
@@ -1878,7 +2150,7 @@ void GemmKernels<TM, TKV>::gateup(hipStream_t st, GemmWorkspace ws, const TM* A,
 
 template <typename TM, typename TKV>
 void GemmKernels<TM, TKV>::logits(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int V, float scale,
-                                  float* logits, unsigned long long* slot, const int* row_stream, const TM* Wt,
+                                  float* logits, unsigned long long* slot, const int* row_stream, const WTiles& Wt,
                                   const RowNorm& rn, int slot_row) {
   EpiLogits<false> e{V, scale, logits, slot, row_stream, slot_row, nullptr, 0};
   run_gemm<TM>(st, ws, A, M, W, d, V, e, GemmKind::Logits, false, Wt, rn);

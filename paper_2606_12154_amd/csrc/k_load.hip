@@ -155,6 +155,67 @@ void q4g32(hipStream_t st, const __bf16* src, size_t rows, int K, unsigned char*
   k_q4g32<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(src, n, K, q4, deq, scale);
 }
 
+__global__ void k_tile_q4(const unsigned char* __restrict__ src, unsigned char* __restrict__ codes,
+                          _Float16* __restrict__ scales, int rows, int K, int interleave_f, int by_k, float scale,
+                          size_t n_chunks) {
+  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n_chunks) return;
+  const int l = (int)(i & 63), nb = K / 128;
+  const size_t t = i >> 6;
+  const int b = (int)(t % nb), rb = (int)(t / nb);
+  const int n = 16 * rb + (l & 15), k0 = 128 * b + 8 * (l >> 4);
+  int row = n;
+  if (interleave_f > 0) {
+    const int c = n & 63, j = (n >> 6) * 32 + (c & 31);
+    row = j < interleave_f ? (c < 32 ? j : interleave_f + j) : -1;
+  }
+  const bool in = row >= 0 && row < rows;
+  const size_t rbytes = by_k ? (size_t)(rows / 2 + rows / 16) : (size_t)(K / 2 + K / 16);
+  // Eight codes in natural order (two to a byte) into one word, element 2 p to
+  // nibble p, 2 p + 1 to nibble p + 4.
+  u32x4 v = {0x88888888u, 0x88888888u, 0x88888888u, 0x88888888u};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (!in) continue;
+    unsigned w = 0;
+    if (by_k) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const unsigned byte = src[(size_t)(k0 + 32 * j + e) * rbytes + row / 2];
+        w |= ((byte >> (4 * (row & 1))) & 15u) << (4 * ((e >> 1) + 4 * (e & 1)));
+      }
+    } else {
+      const unsigned c = *reinterpret_cast<const unsigned*>(src + (size_t)row * rbytes + (k0 + 32 * j) / 2);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) w |= ((c >> (4 * e)) & 15u) << (4 * ((e >> 1) + 4 * (e & 1)));
+    }
+    v[j] = w;
+  }
+  reinterpret_cast<u32x4*>(codes)[i] = v;
+  auto stored = [&](size_t at) { return (_Float16)((float)*reinterpret_cast<const __bf16*>(src + at) * scale); };
+  if (!by_k) {
+    if (l < 16)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        scales[(t * 16 + l) * 4 + j] = in ? stored((size_t)row * rbytes + K / 2 + 2 * (4 * b + j)) : (_Float16)0.f;
+  } else if ((rb & 1) == 0 && (l & 15) == 0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = k0 + 32 * j + e;
+        scales[(size_t)(rb / 2) * K + k] = stored((size_t)k * rbytes + rows / 2 + 2 * (rb / 2));
+      }
+  }
+}
+
+void tile_q4(hipStream_t st, const unsigned char* src, unsigned char* codes, _Float16* scales, int rows, int K,
+             int logical_rows, int interleave_f, bool by_k, float scale) {
+  const size_t n = (size_t)((logical_rows + 15) / 16) * (K / 128) * 64;
+  k_tile_q4<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(src, codes, scales, rows, K, interleave_f, by_k ? 1 : 0, scale,
+                                                         n);
+}
+
 template void transpose<__bf16>(hipStream_t, const __bf16*, __bf16*, int, int);
 template void transpose<float>(hipStream_t, const float*, float*, int, int);
 template void transpose<_Float16>(hipStream_t, const _Float16*, _Float16*, int, int);

@@ -46,6 +46,10 @@ struct Layout {
   // Wo, [Wgate; Wup], Wdown^T and the LM head, K / 2 + K / 16 bytes per row.
   std::vector<size_t> wqkvQ, woQ, wguQ, wdownTQ;
   size_t lm_headQ;
+  // Their operand tiles for <= 32-row GEMMs (multi-stream contexts whose
+  // dimensions are multiples of 128; empty otherwise): codes, then scales.
+  std::vector<size_t> wqkvT4, woT4, wguT4, wdownT4;
+  size_t lm_headT4;
   size_t final_norm, rope, kv, page_table, pos, pending, slot, hist, ll, ll_words, layer_tab, trace;
   size_t row_stream, row_pos, feed, items, x, h, q, qM, o32, oM, m32, mM, part, logits, gemm_ws, gemm_ws_bytes, scratch_u32, split, row_scale;
   // RowNorm buffers of the lockstep decode rows: column-block counters (zero
@@ -104,6 +108,9 @@ size_t step_words(const hh_config& g, size_t cap) {
 int* step_err_word(const hh_config& g, const StepWords& w) {
   return reinterpret_cast<int*>(w.base + step_words(g, w.cap) - 8);
 }
+
+// Bytes of a matrix's 4-bit codes as operand tiles (its scales follow them).
+size_t q4_tile_codes(size_t rows, size_t K) { return (rows + 15) / 16 * 16 * K / 2; }
 
 Layout make_layout(const hh_config& c) {
   Layout L{};
@@ -164,6 +171,16 @@ Layout make_layout(const hh_config& c) {
       L.woQ.push_back(q4(d, hq * 64));
       L.wguQ.push_back(q4(2 * F, d));
       L.wdownTQ.push_back(q4(F, d));
+    }
+    if (c.max_streams > 1 && d % 128 == 0 && F % 128 == 0 && hq * 64 % 128 == 0) {
+      auto tiles4 = [&](size_t rows, size_t K) { return take(q4_tile_codes(rows, K) + (rows + 15) / 16 * 16 * (K / 32) * 2); };
+      L.lm_headT4 = tiles4(V, d);
+      for (int l = 0; l < c.n_layers; ++l) {
+        L.wqkvT4.push_back(tiles4(L.nqkv, d));
+        L.woT4.push_back(tiles4(d, hq * 64));
+        L.wguT4.push_back(tiles4((F + 31) / 32 * 64, d));
+        L.wdownT4.push_back(tiles4(d, F));
+      }
     }
   }
   for (int l = 0; l < c.n_layers; ++l) {
@@ -290,6 +307,24 @@ static bool on_this_device(const hh_ctx* c, const void* p) {
 
 namespace {
 
+// Tiles of a matrix of `rows` logical rows and K columns for the <= 32-row
+// GEMMs: t16 and t4 are its offsets (t4: nullptr when not kept).
+WTiles tiles_at(const hh_ctx* c, size_t t16, const size_t* t4, size_t rows, size_t K, bool by_k) {
+  WTiles t;
+  t.h = c->at<_Float16>(t16);
+  if (t4) {
+    t.q = c->at<unsigned char>(*t4);
+    t.s = c->at<_Float16>(*t4 + q4_tile_codes(rows, K));
+    t.by_k = by_k;
+  }
+  return t;
+}
+WTiles head_tiles(const hh_ctx* c) {
+  const Layout& L = c->L;
+  if (L.wqkvT16.empty()) return WTiles();
+  return tiles_at(c, L.lm_headT16, L.wqkvT4.empty() ? nullptr : &L.lm_headT4, c->cfg.vocab, c->cfg.d_model, false);
+}
+
 KvLayout kv_layout(const hh_ctx* c) { return KvLayout{c->L.n_pages, c->cfg.n_kv_heads, c->L.max_pages}; }
 
 // Enqueue the transformer layers + head for n rows whose bookkeeping
@@ -358,19 +393,26 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
                          flash_prefill_supported(hq / hkv, c->cfg.max_context,
                                                  (size_t)kl.n_pages * 2 * hkv * kPage * kHeadDim);
       // Flash attention reads only the fp16 queries.
-      const bool tiled = !L.wqkvT16.empty();
+      const bool tiled = !L.wqkvT16.empty(), t4 = !L.wqkvT4.empty();
+      WTiles tq, to, tg, td;
+      if (tiled) {
+        tq = tiles_at(c, L.wqkvT16[l], t4 ? &L.wqkvT4[l] : nullptr, L.nqkv, d, false);
+        to = tiles_at(c, L.woT16[l], t4 ? &L.woT4[l] : nullptr, d, hq * 64, false);
+        tg = tiles_at(c, L.wguT16[l], t4 ? &L.wguT4[l] : nullptr, (F + 31) / 32 * 64, d, false);
+        td = tiles_at(c, L.wdownT16[l], t4 ? &L.wdownT4[l] : nullptr, d, F, true);
+      }
       // Lockstep decode rows (one per stream): the attention kernel takes
       // over the QKV split-K reduction, rotation and KV append.
       const bool fold = prefill_stream < 0 && head_row == -1;
       QkvFold<TKV> qf;
       if (fold) {
         const int sp = GK::qkv_deferred(st, gws, h, n, c->at<TM>(L.wqkvM[l]), d, hq, hkv, ws, rs, rp, rope, q, kv, kl, l,
-                                        pt, tiled ? c->at<TM>(L.wqkvT16[l]) : nullptr,
+                                        pt, tq,
                                         pending ? rn_use : RowNorm());
         if (sp > 1) qf = QkvFold<TKV>{gws.ptr, sp, (hq + 2 * hkv) * 64, ws, rope, kv};
       } else {
         GK::qkv(st, gws, h, n, c->at<TM>(L.wqkvM[l]), d, hq, hkv, ws, rs, rp, rope, flash ? nullptr : q,
-                flash ? c->at<TM>(L.qM) : nullptr, kv, kl, l, pt, tiled ? c->at<TM>(L.wqkvT16[l]) : nullptr);
+                flash ? c->at<TM>(L.qM) : nullptr, kv, kl, l, pt, tq);
       }
       if (flash) {
         if constexpr (sizeof(TKV) == 2)
@@ -385,15 +427,14 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
       } else {
         DK::attention_rows(st, n, q, kv, kl, l, pt, rs, rp, hq, hkv, o32, oM, qf);
       }
-      const TM* wo_t = tiled ? c->at<TM>(L.woT16[l]) : nullptr;
       if (fuse) {
-        pending = GK::resid(st, gws, oM, n, c->at<TM>(L.woM[l]), hq * 64, d, ws, x, mn, eps, h, wo_t,
+        pending = GK::resid(st, gws, oM, n, c->at<TM>(L.woM[l]), hq * 64, d, ws, x, mn, eps, h, to,
                             nss, ncnt, L.nrm_ncnt);
       } else {
-        GK::resid(st, gws, oM, n, c->at<TM>(L.woM[l]), hq * 64, d, ws, x, nullptr, 0.f, nullptr, wo_t);
+        GK::resid(st, gws, oM, n, c->at<TM>(L.woM[l]), hq * 64, d, ws, x, nullptr, 0.f, nullptr, to);
         DK::rmsnorm_rows(st, n, x, mn, eps, d, h);
       }
-      GK::gateup(st, gws, h, n, c->at<TM>(L.wguM[l]), d, F, ws, mM, tiled ? c->at<TM>(L.wguT16[l]) : nullptr,
+      GK::gateup(st, gws, h, n, c->at<TM>(L.wguM[l]), d, F, ws, mM, tg,
                  pending ? rn_use : RowNorm());
       // The last layer's down projection takes the final norm along under
       // RowNorm (the head reads h next).
@@ -401,7 +442,7 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
                              : (rnorm && l + 1 == g.n_layers) ? c->at<float>(L.final_norm)
                                                               : nullptr;
       pending = GK::resid(st, gws, mM, n, c->at<TM>(L.wdownM[l]), F, d, ws, x, next_an, eps, h,
-                          tiled ? c->at<TM>(L.wdownT16[l]) : nullptr, next_an ? nss : nullptr, ncnt, L.nrm_ncnt);
+                          td, next_an ? nss : nullptr, ncnt, L.nrm_ncnt);
       if (rnorm && l + 1 == g.n_layers) final_normed = true;
     }
   }
@@ -418,7 +459,7 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
         else DK::rmsnorm_rows(st, n, x, fn, eps, d, h);
       }
       GK::logits(st, gws, h, n, c->at<TM>(L.lm_headM), d, V, ws, logits, slot, rs,
-                 L.wqkvT16.empty() ? nullptr : c->at<TM>(L.lm_headT16), pending ? rn_use : RowNorm());
+                 head_tiles(c), pending ? rn_use : RowNorm());
     }
   }
 }
@@ -596,7 +637,7 @@ void enqueue_head_row(hh_ctx* c, int row, float* logits, unsigned long long* slo
       GK::rmsnorm(st, 1, c->at<float>(L.x) + (size_t)row * g.d_model, g.d_model, c->at<float>(L.final_norm),
                   g.rms_eps, h);
       GK::logits(st, gws, h, 1, c->at<TM>(L.lm_headM), g.d_model, g.vocab, 1.f / c->wscale, logits, slot,
-                 c->at<int>(L.row_stream) + row, L.wqkvT16.empty() ? nullptr : c->at<TM>(L.lm_headT16));
+                 c->at<int>(L.row_stream) + row, head_tiles(c));
       return;
     }
   }
@@ -628,7 +669,7 @@ void enqueue_head_rows(hh_ctx* c, int r0, int n, float* logits, unsigned long lo
   else DK::rmsnorm_rows(c->stream, n, x, fn, g.rms_eps, d, h);
   const GemmWorkspace gws{c->at<float>(L.gemm_ws), L.gemm_ws_bytes};
   GK::logits(c->stream, gws, h, n, c->at<TM>(L.lm_headM), d, g.vocab, 1.f / c->wscale, logits, slot, rs,
-             L.wqkvT16.empty() ? nullptr : c->at<TM>(L.lm_headT16), RowNorm(), n - 1);
+             head_tiles(c), RowNorm(), n - 1);
 }
 
 template <typename TW, typename TKV, typename TM>
@@ -775,7 +816,7 @@ hh_status do_prefill_batch(hh_ctx* c, int n, const int32_t* ids, const int32_t* 
         DK::rmsnorm_rows(st, ne, x, fn, g.rms_eps, d, h);
       }
       GK::logits(st, gws, h, ne, c->at<TM>(L.lm_headM), d, g.vocab, 1.f / c->wscale, nullptr, slot, row_stream,
-                 L.wqkvT16.empty() ? nullptr : c->at<TM>(L.lm_headT16));
+                 head_tiles(c));
       finalize(st, 0, ne, row_stream, row_pos, slot, c->at<int>(L.pending), c->at<int>(L.hist), c->at<int>(L.pos),
                g.max_context);
     }
@@ -1098,6 +1139,20 @@ hh_status hh_load_weights(hh_ctx* c, const void* const* tensors, int32_t n_tenso
         tile16(st, c->at<_Float16>(L.wguM[l]), c->at<_Float16>(L.wguT16[l]), (int)(2 * F), (int)d,
                (int)((F + 31) / 32 * 64), (int)F);
         tile16(st, c->at<_Float16>(L.wdownM[l]), c->at<_Float16>(L.wdownT16[l]), (int)d, (int)F, (int)d, 0);
+      }
+    }
+    if (!L.wqkvT4.empty()) {
+      auto codes = [&](size_t src, size_t dst, size_t rows, size_t K, size_t logical, size_t inter, bool by_k) {
+        tile_q4(st, c->at<unsigned char>(src), c->at<unsigned char>(dst),
+                c->at<_Float16>(dst + q4_tile_codes(logical, K)), (int)rows, (int)K, (int)logical, (int)inter, by_k,
+                c->wscale);
+      };
+      codes(L.lm_headQ, L.lm_headT4, V, d, V, 0, false);
+      for (int l = 0; l < g.n_layers; ++l) {
+        codes(L.wqkvQ[l], L.wqkvT4[l], L.nqkv, d, L.nqkv, 0, false);
+        codes(L.woQ[l], L.woT4[l], d, hq * 64, d, 0, false);
+        codes(L.wguQ[l], L.wguT4[l], 2 * F, d, (F + 31) / 32 * 64, F, false);
+        codes(L.wdownTQ[l], L.wdownT4[l], d, F, d, 0, true);
       }
     }
   } else {
