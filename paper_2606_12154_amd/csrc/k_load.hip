@@ -94,65 +94,104 @@ void tile16(hipStream_t st, const _Float16* src, _Float16* dst, int rows, int K,
   k_tile16<<<(unsigned)((n_chunks + 255) / 256), 256, 0, st>>>(src, dst, rows, K, interleave_f, n_chunks);
 }
 
-// The 4-bit group format: one thread per group of 32 consecutive elements of
-// a row.  Scale s = bf16(max|w| / 7), codes q = clamp(rint(w / s), -8, 7)
-// (fp32 divisions, both roundings to nearest even; s = 0 gives q = 0).  q4
-// (optional) receives the stored row: nibbles n = q + 8 (even element low),
-// then the row's scales as bf16; deq (optional) receives q * s * scale as fp16
-// -- exact, a 4-bit code times an 8-bit significand, for |q s| scale in the
-// fp16 normal range.  deq may be src (each thread reads its whole group before
-// writing it), so neither is declared restrict.
-__global__ void k_q4g32(const __bf16* src, size_t n_groups, int K, unsigned char* __restrict__ q4, _Float16* deq,
-                        float scale) {
-  const size_t gi = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (gi >= n_groups) return;
-  const int gpr = K / 32;
-  const size_t row = gi / gpr;
-  const int g = (int)(gi % gpr);
-  const size_t e0 = row * (size_t)K + 32 * (size_t)g;
-  float v[32];
+// The 4-bit group format: groups of 32 consecutive elements of a row.  Scale
+// s = bf16(max|w| / 7), codes q = clamp(rint(w / s), -8, 7) (fp32 divisions,
+// both roundings to nearest even; s = 0 gives q = 0).  q4 (optional) receives
+// the stored row: nibbles n = q + 8 (even element low), then the row's scales
+// as bf16; deq (optional) receives q * s * scale as fp16 -- exact, a 4-bit code
+// times an 8-bit significand, for |q s| scale in the fp16 normal range.  deq
+// may be src (each thread reads its elements before writing them), so neither
+// is declared restrict.
+//
+// Four lanes hold a group, eight elements each, so a wave reads 1 KiB and
+// writes 256 bytes of codes in one piece; a thread has kQ4Groups such pieces in
+// flight, 64 groups apart, and finds its row by one division.
+// With a thread per group (16-byte loads 64 bytes apart) and a division per
+// element the kernel was bound by its arithmetic: ~20 instructions an element.
+// The quotient of two bf16 values w / s is a tie between codes, and then a
+// short binary fraction, or 2^-10 or more away from one (8-bit significands).
+// w times the reciprocal with one residual correction is exact for the first
+// and within 2^-20 for the second, so its rounding is the division's.  128,256 x
+// 2,048: 136.9 -> 122 us, with non-temporal loads and stores 110.9 us (6.1 TB/s;
+// one, two, eight pieces a thread 127, 112, 127 us).
+constexpr int kQ4Groups = 4;
+template <bool CODES, bool DEQ>
+__global__ __launch_bounds__(256) void k_q4g32(const __bf16* src, size_t n_groups, int K, int row_step, int group_step,
+                                               unsigned char* __restrict__ q4, _Float16* deq, float scale) {
+  const int gpr = K / 32, sub = threadIdx.x & 3;
+  const size_t g0 = (size_t)blockIdx.x * (64 * kQ4Groups) + (threadIdx.x >> 2);
+  size_t row = n_groups >> 32 ? g0 / gpr : (unsigned)g0 / (unsigned)gpr;
+  int g = (int)(g0 - row * gpr);
+  u32x4 t[kQ4Groups];
 #pragma unroll
-  for (int c = 0; c < 4; ++c) {
-    const u32x4 t = *reinterpret_cast<const u32x4*>(src + e0 + 8 * c);
-    float f[8];
-    widen16(t, f, __bf16());
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[8 * c + i] = f[i];
+  for (int u = 0; u < kQ4Groups; ++u) {
+    t[u] = u32x4{0u, 0u, 0u, 0u};
+    const size_t gi = g0 + 64 * u;
+    if (gi < n_groups) t[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + 32 * gi + 8 * sub));
   }
-  float a = 0.f;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) a = fmaxf(a, fabsf(v[i]));
-  const __bf16 sb = (__bf16)(a / 7.0f);
-  const float sf = (float)sb;
-  unsigned nib[4] = {0u, 0u, 0u, 0u};
-  _Float16 dq[32];
+  for (int u = 0; u < kQ4Groups; ++u) {
+    const size_t gi = g0 + 64 * u;
+    float v[8];
+    widen16(t[u], v, __bf16());
+    float a = 0.f;
 #pragma unroll
-  for (int i = 0; i < 32; ++i) {
-    const float r = sf > 0.f ? v[i] / sf : 0.f;
-    const int q = min(7, max(-8, (int)rintf(r)));
-    nib[i >> 3] |= (unsigned)(q + 8) << (4 * (i & 7));
-    dq[i] = (_Float16)((float)q * sf * scale);
-  }
-  if (q4) {
-    unsigned char* rb = q4 + row * (size_t)(K / 2 + K / 16);
-    *reinterpret_cast<u32x4*>(rb + 16 * g) = u32x4{nib[0], nib[1], nib[2], nib[3]};
-    *reinterpret_cast<__bf16*>(rb + K / 2 + 2 * g) = sb;
-  }
-  if (deq) {
+    for (int i = 0; i < 8; ++i) a = fmaxf(a, fabsf(v[i]));
+    // The quad's lanes 1 and 2 away (all lanes take part; a group is all there
+    // or all past the end).
+    a = fmaxf(a, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, a), 0xB1, 0xF, 0xF, true)));
+    a = fmaxf(a, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, a), 0x4E, 0xF, 0xF, true)));
+    const __bf16 sb = (__bf16)(a / 7.0f);
+    const float sf = (float)sb;
+    int q[8];
+    if (sf >= 0x1p-100f && sf <= 0x1p100f) {
+      // |w / s| < 7.5 here: no clamp.  (A NaN element gives 0 either way.)
+      const float inv = __builtin_amdgcn_rcpf(sf);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      typedef _Float16 f16x8l __attribute__((ext_vector_type(8)));
-      f16x8l o;
+      for (int i = 0; i < 8; ++i) {
+        const float r = v[i] * inv;
+        q[i] = (int)rintf(fmaf(fmaf(-r, sf, v[i]), inv, r));
+      }
+    } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = dq[8 * c + i];
-      *reinterpret_cast<f16x8l*>(deq + e0 + 8 * c) = o;
+      for (int i = 0; i < 8; ++i) {
+        const float r = sf > 0.f ? v[i] / sf : 0.f;
+        q[i] = min(7, max(-8, (int)rintf(r)));
+      }
+    }
+    if (gi < n_groups) {
+      if constexpr (CODES) {
+        unsigned char* rb = q4 + row * (size_t)(K / 2 + K / 16);
+        unsigned n = 0x88888888u;  // every field q + 8 ends in 0 .. 15
+#pragma unroll
+        for (int i = 0; i < 8; ++i) n += (unsigned)q[i] << (4 * i);
+        __builtin_nontemporal_store(n, reinterpret_cast<unsigned*>(rb + 16 * g + 4 * sub));
+        if (sub == 0) *reinterpret_cast<__bf16*>(rb + K / 2 + 2 * g) = sb;
+      }
+      if constexpr (DEQ) {
+        f16x8 o;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = (_Float16)((float)q[i] * sf * scale);
+        *reinterpret_cast<f16x8*>(deq + 32 * gi + 8 * sub) = o;
+      }
+    }
+    row += row_step;
+    g += group_step;
+    if (g >= gpr) {
+      g -= gpr;
+      ++row;
     }
   }
 }
 
 void q4g32(hipStream_t st, const __bf16* src, size_t rows, int K, unsigned char* q4, _Float16* deq, float scale) {
-  const size_t n = rows * (size_t)(K / 32);
-  k_q4g32<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(src, n, K, q4, deq, scale);
+  const int gpr = K / 32;
+  const size_t n = rows * (size_t)gpr;
+  const unsigned grid = (unsigned)((n + 64 * kQ4Groups - 1) / (64 * kQ4Groups));
+  const int rs = 64 / gpr, gs = 64 % gpr;
+  if (q4 && deq) k_q4g32<true, true><<<grid, 256, 0, st>>>(src, n, K, rs, gs, q4, deq, scale);
+  else if (q4) k_q4g32<true, false><<<grid, 256, 0, st>>>(src, n, K, rs, gs, q4, deq, scale);
+  else k_q4g32<false, true><<<grid, 256, 0, st>>>(src, n, K, rs, gs, q4, deq, scale);
 }
 
 __global__ void k_tile_q4(const unsigned char* __restrict__ src, unsigned char* __restrict__ codes,
