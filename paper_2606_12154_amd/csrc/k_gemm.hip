@@ -1920,7 +1920,7 @@ struct TileCfg {
 // the CUs 56); QKV 128 x 128 to 1,024 rows and 256 x 128 above (8,192: 114, 256
 // x 256 132, 128 x 128 134); down 8,192 rows 256 x 256 236 (128 x 128 302),
 // 1,024 rows 128 x 128 in two splits 47.
-static TileCfg fit_tile(GemmKind kind, int M, int n_cols, int K, int max_splits) {
+static TileCfg fit_tile(GemmKind kind, int M, int n_cols, int K, int max_splits, double* us = nullptr) {
   struct Cand {
     int bm, bn;
     double step, tail, tail_qkv;
@@ -1941,7 +1941,37 @@ static TileCfg fit_tile(GemmKind kind, int M, int n_cols, int K, int max_splits)
         best = TileCfg{c.bm, c.bn, splits};
       }
     }
+  if (us) *us = least;
   return best;
+}
+
+// Gate/up rows that go to a first launch of full rounds (0: one launch for
+// all).  A last round that holds a few row tiles costs as much as a full one
+// (3,168 rows: 832 tiles of 256 x 256 on 256 CUs, 3.25 rounds, take four), so
+// the last rows go to a launch of their own where its estimate and ~5 us
+// between the two come to less.  Up to 128 rows that launch is the mid
+// kernel's (~0.55 us a step and ~5 us, one round of 256 blocks of 64 columns).
+// Whole 1B prefills, one launch / two: 1,100 rows 4.05 / 3.92 ms, 1,230 4.15 /
+// 4.00, 2,100 6.74 / 6.33, 2,500 7.18 / 7.09, 32 prompts of 99 10.56 / 10.40.
+static int gateup_first_rows(int M, int n_cols, int K) {
+  if (getenv("HH_GEMM_GATEUP")) return 0;
+  double whole = 0.0;
+  fit_tile(GemmKind::GateUp, M, n_cols, K, 1, &whole);
+  int first = 0;
+  double least = 0.95 * whole;
+  for (int k = 0; k < 4; ++k) {
+    const int m1 = (M - 1) / 256 * 256 - 256 * k, rest = M - m1;
+    if (m1 < 512) break;
+    double t = 0.0, t2 = 0.0;
+    fit_tile(GemmKind::GateUp, m1, n_cols, K, 1, &t);
+    if (rest > 128) fit_tile(GemmKind::GateUp, rest, n_cols, K, 1, &t2);
+    else t2 = (double)((n_cols / 64 + 255) / 256) * (K / 64 * 0.55 + 5.0);
+    if (t + t2 + 5.0 < least) {
+      least = t + t2 + 5.0;
+      first = m1;
+    }
+  }
+  return first;
 }
 
 static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
@@ -2145,7 +2175,18 @@ void GemmKernels<TM, TKV>::gateup(hipStream_t st, GemmWorkspace ws, const TM* A,
                                   TM* m, const WTiles& Wt, const RowNorm& rn) {
   // Groups of 32 gate + 32 up columns: every tile width here is a multiple of 64.
   EpiGateUp<TM> e{F, 32, scale, m};
-  run_gemm<TM>(st, ws, A, M, W, d, ((F + 31) / 32) * 64, e, GemmKind::GateUp, false, Wt, rn);
+  const int n_cols = ((F + 31) / 32) * 64;
+  if constexpr (sizeof(TM) == 2) {
+    // (run_gemm scales all of A's rows for a RowNorm request: one launch then.)
+    const int first = M > 512 && n_cols >= 8192 && d % 64 == 0 && !rn.ss_in ? gateup_first_rows(M, n_cols, d) : 0;
+    if (first > 0) {
+      run_gemm<TM>(st, ws, A, first, W, d, n_cols, e, GemmKind::GateUp, false, Wt, rn);
+      A += (size_t)first * d;
+      e.m += (size_t)first * F;
+      M -= first;
+    }
+  }
+  run_gemm<TM>(st, ws, A, M, W, d, n_cols, e, GemmKind::GateUp, false, Wt, rn);
 }
 
 template <typename TM, typename TKV>
