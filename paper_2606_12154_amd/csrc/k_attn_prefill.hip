@@ -76,10 +76,14 @@ struct FlashCfg {
 
 // PACK: the pass holds rows of several streams; workgroup blockIdx.x takes the
 // query-block pair of items[blockIdx.x] instead of pair blockIdx.x of one
-// stream's rows.  Its queries come as fp32 and enter the products as fp16
-// high and low parts, and so do the softmax weights: such rows were attended
-// in fp32 (the row kernel of lockstep decoding, one workgroup per row and kv
-// head), and two terms of 11 bits keep that precision.
+// stream's rows.  Such rows were attended in fp32 (the row kernel of lockstep
+// decoding, one workgroup per row and kv head), so queries (which come as
+// fp32) and softmax weights enter the products as fp16 high and low parts,
+// both scaled by powers of two, without which the parts would end at fp16's
+// range: a query row so that its largest value is in [2^13, 2^14), which keeps
+// 22 bits or more of every value above 2^-15 of it, and all else to 2^-38 of
+// it; weights by 2^11, so that they are at most 2^15 and held to 2^-22 of
+// themselves or 2^-36 of the row's largest (131,072 keys: 2^-19 of their sum).
 template <int G, int NS, bool PACK>
 __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* __restrict__ qM,
                                                                const float* __restrict__ q32,
@@ -128,25 +132,40 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
   const int qrow = q0 + c;
   const bool qvalid = active && qrow < n_rows;
   const int qpos = p0 + qrow;
-  const float scale = 0.125f * 1.4426950408889634f;  // 1/sqrt(64) * log2(e)
+  float scale = 0.125f * 1.4426950408889634f;  // 1/sqrt(64) * log2(e); PACK: over the query row's scale
 
   f16x8 qf[4], ql[PACK ? 4 : 1];  // ql: low parts
+  if constexpr (PACK) {
+    // A lane holds half of its query row, lane ^ 32 the other half.
+    f32x4 qv[8];
+    float mx = 0.f;
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-    qf[ks] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    if constexpr (PACK) {
-      ql[ks] = qf[ks];
-      if (qvalid) {
-        const f32x4* src = reinterpret_cast<const f32x4*>(q32 + ((size_t)qrow * hq + j) * 64 + 16 * ks + 8 * h);
+    for (int i = 0; i < 8; ++i) {
+      qv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (qvalid)
+        qv[i] = *reinterpret_cast<const f32x4*>(q32 + ((size_t)qrow * hq + j) * 64 + 16 * (i >> 1) + 8 * h + 4 * (i & 1));
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float v = src[e >> 2][e & 3];
-          qf[ks][e] = (_Float16)v;
-          ql[ks][e] = (_Float16)(v - (float)qf[ks][e]);
-        }
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, fabsf(qv[i][e]));
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    int ex = 0;  // mx = f 2^ex, f in [0.5, 1)
+    if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &ex);
+    const int up = min(14 - ex, 100);
+    const float f = ldexpf(1.f, up);
+    scale *= ldexpf(1.f, -up);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float v = qv[i][e] * f;
+        qf[i >> 1][4 * (i & 1) + e] = (_Float16)v;
+        ql[i >> 1][4 * (i & 1) + e] = (_Float16)(v - (float)qf[i >> 1][4 * (i & 1) + e]);
       }
-    } else if (qvalid) {
-      qf[ks] = *reinterpret_cast<const f16x8*>(qM + ((size_t)qrow * hq + j) * 64 + 16 * ks + 8 * h);
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      qf[ks] = f16x8{0, 0, 0, 0, 0, 0, 0, 0};
+      if (qvalid) qf[ks] = *reinterpret_cast<const f16x8*>(qM + ((size_t)qrow * hq + j) * 64 + 16 * ks + 8 * h);
     }
   }
   float m = -INFINITY, lsum = 0.f;
@@ -227,8 +246,10 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
     // factor keeps the order), and a query's reference m moves only when
     // the block's max exceeds it by more than kLazy (log2 units), so the
     // output is rescaled in few blocks (alpha is exactly 1 otherwise).
-    // Weights are then at most 2^kLazy, which fp16 holds with its full
-    // relative precision; the final (m, l, o) stay consistent.
+    // Weights are then at most 2^kLazy (PACK: 2^(kLazy + kShift), the shift in
+    // the exponent's FMA and in l and o alike), which fp16 holds with its full
+    // relative precision; the final (m, l, o) stay consistent.  PACK moves m in
+    // whole steps, so that kShift - m and the differences of m are exact.
     if (k0 + 31 > p0 + q0 || k0 + 32 > kend) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -242,17 +263,18 @@ __global__ __launch_bounds__(64 * G * NS) void k_flash_prefill(const _Float16* _
     bm = fmaxf(bm, __shfl_xor(bm, 32, 64)) * scale;
     // A group's first blocks may hide every key from some query of an
     // appended chunk: keep such a query's state at (-inf, 0, 0).
-    constexpr float kLazy = 8.f;
-    const float mn = bm > m + kLazy ? bm : m;  // m = -inf: any finite bm
+    constexpr float kLazy = PACK ? 4.f : 8.f, kShift = PACK ? 11.f : 0.f;
+    const float mn = bm > m + kLazy ? (PACK ? ceilf(bm) : bm) : m;  // m = -inf: any finite bm
     const float mref = mn == -INFINITY ? 0.f : mn;
-    // Hardware exp2 (arguments are <= 0 up to the product's rounding; results
+    const float nref = kShift - mref;
+    // Hardware exp2 (arguments are <= kLazy + kShift up to the product's rounding; results
     // below the normal range flush to zero, which a softmax weight can take).
     const float alpha = __builtin_amdgcn_exp2f(m - mref);
     float ls = 0.f;
     f16x8 pb[2], pl[PACK ? 2 : 1];  // pl: low parts
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-      const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[i], scale, -mref));
+      const float pv = __builtin_amdgcn_exp2f(fmaf(sacc[i], scale, nref));
       ls += pv;
       pb[i >> 3][i & 7] = (_Float16)pv;
       if constexpr (PACK) pl[i >> 3][i & 7] = (_Float16)(pv - (float)pb[i >> 3][i & 7]);
