@@ -124,13 +124,14 @@ struct GemmKernels {
   static void logits(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const TM* W, int d, int V, float scale, float* logits,
                      unsigned long long* slot, const int* row_stream, const WTiles& Wt = WTiles(),
                      const RowNorm& rn = RowNorm(), int slot_row = -1);
-  // Final norm and LM head of M rows of x on fp16 operands at the precision
-  // of 32-bit inputs (16-bit TM only): split holds 32 ceil(M / 16) rows of d
-  // halfs, row_scale M floats.  Here and in logits: the greedy key of row
-  // slot_row (-1: of every row) goes to its stream's slot.
-  static void logits_split(hipStream_t st, const float* x, int M, const float* gain, float eps, _Float16* split,
-                           float* row_scale, const TM* W, int d, int V, float scale, float* logits,
-                           unsigned long long* slot, const int* row_stream, int slot_row);
+  // Final norm and LM head of M rows of x at the precision of 32-bit inputs
+  // and of the one-row head's sums.  16-bit TM: rows holds 32 ceil(M / 16) rows
+  // of d halfs, row_scale M floats; fp32: rows holds M rows of d.  Here and in
+  // logits: the greedy key of row slot_row (-1: of every row) goes to its
+  // stream's slot.
+  static void logits_rows(hipStream_t st, const float* x, int M, const float* gain, float eps, TM* rows,
+                          float* row_scale, const TM* W, int d, int V, float scale, float* logits,
+                          unsigned long long* slot, const int* row_stream, int slot_row);
 };
 
 // ---- causal flash attention for prefill rows of one stream (k_attn_prefill.hip)

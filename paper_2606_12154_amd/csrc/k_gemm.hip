@@ -283,10 +283,24 @@ struct EpiGateUp {
   }
 };
 
+// s += a, and what the addition rounds off goes to rest (exactly where |s| is
+// the larger, else to the rounding of the difference).
+__device__ __forceinline__ void add_rest(f32x4& s, const f32x4& a, f32x4& rest) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float t = s[e] + a[e];
+    rest[e] += a[e] - (t - s[e]);
+    s[e] = t;
+  }
+}
+
 // LM head rows: optional fp32 logits, and the packed argmax of row slot_row (-1:
 // of every row) into the row's stream slot.  PAIR (tile kernel only): blocks
 // of 32 rows of A hold 16 rows' fp16 high parts and then their low parts,
-// scaled per row (k_norm_split): the two products are added and scaled back.
+// scaled per row (k_norm_rows): the two products are added and scaled back.
+// Each K step's high products are added up apart from the running sum
+// (kPairSums, add_rest): 2,048 products in one chain of MFMA accumulations have
+// twice the error of the one-row head's 64 chains.
 template <bool PAIR>
 struct EpiLogits {
   int V;
@@ -393,6 +407,10 @@ struct EpiLogits {
     }
   }
 };
+template <class Epi>
+constexpr bool kPairSums = false;
+template <>
+constexpr bool kPairSums<EpiLogits<true>> = true;
 
 // ---------------------------------------------------------------- generic kernel (64 x 64)
 
@@ -401,7 +419,10 @@ struct EpiLogits {
 constexpr int GBM = 64, GBN = 64, GBK = 32;
 constexpr int GLDC = GBN + 4;
 
-template <typename TM, typename Epi>
+// SUMS (fp32 operands): products of 16 k at a time are added to sums that keep
+// their roundings apart, for rows whose sums must be as good as those of the
+// one-row head (64 chains a row).
+template <typename TM, typename Epi, bool SUMS = false>
 __global__ __launch_bounds__(256) void k_gemm(const TM* __restrict__ A, int M, const TM* __restrict__ W, int K,
                                               Epi epi) {
   constexpr int V = Vec16<TM>::n;  // elements per 16-byte chunk
@@ -414,11 +435,14 @@ __global__ __launch_bounds__(256) void k_gemm(const TM* __restrict__ A, int M, c
   const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
   const int wm = wv >> 1, wn = wv & 1;
   const int lr = lane & 15, lk = lane >> 4;
-  f32x4 acc[2][2];
+  f32x4 acc[2][2], sum[SUMS ? 2 : 1][2], rest[SUMS ? 2 : 1][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 2; ++j) {
+      acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (SUMS) sum[i][j] = rest[i][j] = acc[i][j];
+    }
 
   for (int k0 = 0; k0 < K; k0 += GBK) {
     for (int c = tid; c < GBM * CPR; c += 256) {
@@ -457,9 +481,28 @@ __global__ __launch_bounds__(256) void k_gemm(const TM* __restrict__ A, int M, c
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
+        if constexpr (SUMS) {
+          if (kk % 16 == 12)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+              for (int j = 0; j < 2; ++j) {
+                add_rest(sum[i][j], acc[i][j], rest[i][j]);
+                acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+              }
+        }
       }
     }
     __syncthreads();
+  }
+  if constexpr (SUMS) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)  // (an overflowed sum stays infinite)
+          acc[i][j][e] = sum[i][j][e] + (fabsf(rest[i][j][e]) < INFINITY ? rest[i][j][e] : 0.f);
   }
   // Output fragment layout: lane holds C[4 * lk + e][lr] of its 16x16 fragment.
 #pragma unroll
@@ -832,6 +875,10 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
              16 * ((4 * kb + h) ^ (((l15 >> 1) & 1) | ((l15 >> 2) << 1)));
   }
   f32x4 acc[T::FM][T::FN];
+  // kPairSums: the high parts' sums over the steps so far (their roundings go
+  // to the low parts' accumulators); acc holds one step's.
+  constexpr bool SUMS = kPairSums<Epi>;
+  f32x4 sum[SUMS ? T::FM / 2 : 1][T::FN];
   f16x8 a[2][T::FM], b[2][T::FN];
   auto frags = [&](int kb, unsigned so) {
     const lds_char* base = (const lds_char*)smem + so;
@@ -845,7 +892,8 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
     for (int i = 0; i < T::FM; ++i)
 #pragma unroll
       for (int j = 0; j < T::FN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(b[kb][j], a[kb][i], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+            b[kb][j], a[kb][i], SUMS && kb == 0 && i % 2 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
   };
   constexpr int NRD = T::FM + T::FN;
   constexpr int kWaitLds = 0xF | (0x7 << 4) | (0x3 << 14);  // lgkmcnt(0)
@@ -863,6 +911,12 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
     for (int i = 0; i < T::FM; ++i)
 #pragma unroll
       for (int j = 0; j < T::FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int i = 0; i < T::FM / 2; ++i)
+#pragma unroll
+        for (int j = 0; j < T::FN; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
     for (int step = 0; step < u.nk; ++step) {
       const unsigned sn = so + T::STAGE == T::LDS ? 0u : so + T::STAGE;
       __builtin_amdgcn_sched_barrier(0);
@@ -888,8 +942,20 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
         if (k < NRD) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (SUMS) {
+#pragma unroll
+        for (int i = 0; i < T::FM / 2; ++i)
+#pragma unroll
+          for (int j = 0; j < T::FN; ++j) add_rest(sum[i][j], acc[2 * i][j], acc[2 * i + 1][j]);
+      }
       cursor_next();
       so = sn;
+    }
+    if constexpr (SUMS) {
+#pragma unroll
+      for (int i = 0; i < T::FM / 2; ++i)
+#pragma unroll
+        for (int j = 0; j < T::FN; ++j) acc[2 * i][j] = sum[i][j];
     }
     const int row0 = u.m0 + wm * T::WM + l15, cb = u.n0 + wn * 64;
     if (partial) {
@@ -2199,56 +2265,76 @@ void GemmKernels<TM, TKV>::logits(hipStream_t st, GemmWorkspace ws, const TM* A,
 
 // ---------------------------------------------------------------- LM head of many rows
 
-// Final RMSNorm of one row per workgroup into fp16 high and low parts: row r of
-// x goes to rows 32 (r / 16) + r % 16 and + 16 of out, times the power of two
-// that puts its largest value in [2^13, 2^14) (row_scale[r]: the inverse), so
-// the low parts keep 22 bits of the row's largest value whatever its size.
-__global__ __launch_bounds__(256) void k_norm_split(const float* __restrict__ x, int N, const float* __restrict__ gain,
-                                                    float eps, _Float16* __restrict__ out,
-                                                    float* __restrict__ row_scale) {
-  __shared__ float red[4];
+// Final RMSNorm of one row per workgroup, in 64 bits up to the stored value.
+// SPLIT: into fp16 high and low parts: row r of x goes to rows 32 (r / 16) +
+// r % 16 and + 16 of out, times the power of two that puts its largest value
+// in [2^13, 2^14) (row_scale[r]: the inverse); the parts hold a value to 2^-23
+// of itself or 2^-38 of the row's largest.  Else into fp32 rows.
+template <bool SPLIT, typename TO>
+__global__ __launch_bounds__(256) void k_norm_rows(const float* __restrict__ x, int N, const float* __restrict__ gain,
+                                                   float eps, TO* __restrict__ out, float* __restrict__ row_scale) {
+  __shared__ double red[4];
+  __shared__ float redm[4];
   const int row = blockIdx.x;
   const float* xr = x + (size_t)row * N;
-  float ss = 0.f;
-  for (int k = threadIdx.x; k < N; k += 256) ss += xr[k] * xr[k];
-  const float inv = rsqrtf(block_sum256(ss, red) / (float)N + eps);
-  float mx = 0.f;
-  for (int k = threadIdx.x; k < N; k += 256) mx = fmaxf(mx, fabsf(xr[k] * inv * gain[k]));
-  mx = wave_max(mx);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
+  double ss = 0.0;
+  for (int k = threadIdx.x; k < N; k += 256) ss += (double)xr[k] * xr[k];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
   __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  int e = 0;  // mx = f 2^e, f in [0.5, 1)
-  if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &e);
-  const float up = ldexpf(1.f, min(14 - e, 126));
-  if (threadIdx.x == 0) row_scale[row] = 1.f / up;
-  _Float16* hi = out + (size_t)(32 * (row >> 4) + (row & 15)) * N;
-  _Float16* lo = hi + (size_t)16 * N;
-  for (int k = threadIdx.x; k < N; k += 256) {
-    const float v = xr[k] * inv * gain[k] * up;
-    const _Float16 a = (_Float16)v;
-    hi[k] = a;
-    lo[k] = (_Float16)(v - (float)a);
+  const double inv = 1.0 / sqrt((red[0] + red[1] + red[2] + red[3]) / N + eps);
+  if constexpr (!SPLIT) {
+    for (int k = threadIdx.x; k < N; k += 256) out[(size_t)row * N + k] = (TO)(xr[k] * inv * gain[k]);
+  } else {
+    float mx = 0.f;
+    for (int k = threadIdx.x; k < N; k += 256) mx = fmaxf(mx, fabsf((float)(xr[k] * inv * gain[k])));
+    mx = wave_max(mx);
+    if ((threadIdx.x & 63) == 0) redm[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(redm[0], redm[1]), fmaxf(redm[2], redm[3]));
+    int e = 0;  // mx = f 2^e, f in [0.5, 1)
+    if (mx > 0.f && mx < INFINITY) (void)frexpf(mx, &e);
+    const float up = ldexpf(1.f, min(14 - e, 126));
+    if (threadIdx.x == 0) row_scale[row] = 1.f / up;
+    TO* hi = out + (size_t)(32 * (row >> 4) + (row & 15)) * N;
+    TO* lo = hi + (size_t)16 * N;
+    for (int k = threadIdx.x; k < N; k += 256) {
+      const double v = xr[k] * inv * gain[k] * up;
+      const TO a = (TO)(float)v;
+      hi[k] = a;
+      lo[k] = (TO)(float)(v - (double)(float)a);
+    }
   }
 }
 
 // A row's logits were 32-bit products of the row with the weights, one pass
 // over the LM head per row (84 us each on the 1B model).  Two fp16 terms per
 // value keep that precision on the matrix cores, and the rows share the pass.
+// Relative error (2-norm) against 64 bits, one-row head / one MFMA chain per
+// sum / sums kept apart from their roundings: bf16 d 2,048 1.21 / 2.82 / 0.66
+// 1e-7, d 256 0.94 / 1.25 / 0.71; fp32 d 2,048 0.99 / 7.8 / 0.75, d 256 0.90 /
+// 2.9 / 0.81.  200 rows of the 1B head (with the call's ~110 us of other work)
+// 16,340 / 319 / 398 us, fp32 31,020 / 1,686 / 1,848 us.
 template <typename TM, typename TKV>
-void GemmKernels<TM, TKV>::logits_split(hipStream_t st, const float* x, int M, const float* gain, float eps,
-                                        _Float16* split, float* row_scale, const TM* W, int d, int V, float scale,
-                                        float* logits, unsigned long long* slot, const int* row_stream, int slot_row) {
+void GemmKernels<TM, TKV>::logits_rows(hipStream_t st, const float* x, int M, const float* gain, float eps, TM* rows,
+                                       float* row_scale, const TM* W, int d, int V, float scale, float* logits,
+                                       unsigned long long* slot, const int* row_stream, int slot_row) {
   if constexpr (sizeof(TM) == 2) {
-    k_norm_split<<<M, 256, 0, st>>>(x, d, gain, eps, split, row_scale);
+    _Float16* split = reinterpret_cast<_Float16*>(rows);
+    k_norm_rows<true, _Float16><<<M, 256, 0, st>>>(x, d, gain, eps, split, row_scale);
     EpiLogits<true> e{V, scale, logits, slot, row_stream, slot_row, row_scale, M};
-    const int rows = 32 * ((M + 15) / 16);
-    const TileCfg c = fit_tile(GemmKind::Logits, rows, V, d, 1);
+    const int n = 32 * ((M + 15) / 16);
+    const TileCfg c = fit_tile(GemmKind::Logits, n, V, d, 1);
     const GemmWorkspace none{nullptr, 0};
     const _Float16* Wh = reinterpret_cast<const _Float16*>(W);
-    if (c.bm == 256 && c.bn == 256) launch_tile<256, 256>(st, none, split, rows, Wh, d, V, 1, e, true);
-    else if (c.bm == 256) launch_tile<256, 128>(st, none, split, rows, Wh, d, V, 1, e, true);
-    else launch_tile<128, 128>(st, none, split, rows, Wh, d, V, 1, e, true);
+    // (256 x 256 tiles leave no registers for the sums.)
+    if (c.bm == 256) launch_tile<256, 128>(st, none, split, n, Wh, d, V, 1, e, true);
+    else launch_tile<128, 128>(st, none, split, n, Wh, d, V, 1, e, true);
+  } else {
+    k_norm_rows<false, TM><<<M, 256, 0, st>>>(x, d, gain, eps, rows, nullptr);
+    EpiLogits<false> e{V, scale, logits, slot, row_stream, slot_row, nullptr, 0};
+    k_gemm<TM, EpiLogits<false>, true><<<dim3((V + GBN - 1) / GBN, (M + GBM - 1) / GBM), 256, 0, st>>>(rows, M, W, d, e);
   }
 }
 

@@ -658,12 +658,13 @@ void enqueue_head_rows(hh_ctx* c, int r0, int n, float* logits, unsigned long lo
   float* x = c->at<float>(L.x) + (size_t)r0 * d;
   const int* rs = c->at<int>(L.row_stream) + r0;
   const float* fn = c->at<float>(L.final_norm);
-  if (sizeof(TM) == 2 && g.weight_format == HH_WF_DTYPE) {
-    GK::logits_split(c->stream, x, n, fn, g.rms_eps, c->at<_Float16>(L.split), c->at<float>(L.row_scale),
-                     c->at<TM>(L.lm_headM), d, g.vocab, 1.f / c->wscale, logits, slot, rs, n - 1);
+  if (g.weight_format == HH_WF_DTYPE) {
+    TM* rows = c->at<TM>(sizeof(TM) == 2 ? L.split : L.h);
+    GK::logits_rows(c->stream, x, n, fn, g.rms_eps, rows, c->at<float>(L.row_scale), c->at<TM>(L.lm_headM), d, g.vocab,
+                    1.f / c->wscale, logits, slot, rs, n - 1);
     return;
   }
-  // fp32 models, and 4-bit ones, whose head takes fp16 rows.
+  // 4-bit models: the head takes fp16 rows.
   TM* h = c->at<TM>(L.h);
   if (GK::norm_fusable(d)) GK::rmsnorm(c->stream, n, x, d, fn, g.rms_eps, h);
   else DK::rmsnorm_rows(c->stream, n, x, fn, g.rms_eps, d, h);
