@@ -659,6 +659,15 @@ void enqueue_head_rows(hh_ctx* c, int r0, int n, float* logits, unsigned long lo
   const int* rs = c->at<int>(L.row_stream) + r0;
   const float* fn = c->at<float>(L.final_norm);
   if (g.weight_format == HH_WF_DTYPE) {
+    // The shared pass costs as much for one row as for 32, the one-row head its
+    // own pass over the weights for each (1B head, calls of one / two / three
+    // rows: bf16 159 / 246 / 330 us against 195 .. 205, fp32 316 / 473 / 630
+    // against 550).
+    if (n <= (sizeof(TM) == 2 ? 1 : 2)) {
+      for (int i = 0; i < n; ++i)
+        enqueue_head_row<TW, TKV, TM>(c, r0 + i, logits + (size_t)i * g.vocab, i + 1 == n ? slot : nullptr);
+      return;
+    }
     TM* rows = c->at<TM>(sizeof(TM) == 2 ? L.split : L.h);
     GK::logits_rows(c->stream, x, n, fn, g.rms_eps, rows, c->at<float>(L.row_scale), c->at<TM>(L.lm_headM), d, g.vocab,
                     1.f / c->wscale, logits, slot, rs, n - 1);
