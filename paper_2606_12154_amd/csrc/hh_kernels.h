@@ -148,6 +148,13 @@ struct FlashItem {
   int row, rows;    // that row's index in the pass, and how many rows follow
   int pair;
 };
+// What decides between it and the row kernel (attention_rows): the pass's rows
+// and items, the sums of keys over both, and the longest stream's keys.
+struct PackedRows {
+  int rows = 0, items = 0, longest = 0;
+  double row_keys = 0, item_keys = 0;
+};
+bool flash_packed_wins(const PackedRows& p, int G, int hkv);
 void flash_prefill_packed(hipStream_t st, const float* q, const _Float16* kv, KvLayout L, int layer,
                           const int* page_table, const FlashItem* items, int n_items, int hq, int hkv, _Float16* oM);
 

@@ -21,6 +21,8 @@
 // 8(i/4) + 4(l/32) + i%4, column l%32.
 #include "hh_kernels.h"
 
+#include <algorithm>
+
 namespace hh {
 
 constexpr int kFlashMaxPages = 8192;  // pages of keys per prefill attention (131072 positions)
@@ -418,6 +420,27 @@ void flash_prefill(hipStream_t st, const _Float16* qM, const _Float16* kv, KvLay
     launch_flash<8, 2, false>(st, grid, qM, nullptr, kv, L, layer, page_table, nullptr, s, p0, n_rows, hq, oM);
 }
 
+// The row kernel serves a pass whose rows are few (fewer than 1.5 of its
+// workgroups per CU: a chain over a stream's keys is then longer here), and
+// with four heads per kv head one whose streams have few rows each, since an
+// item's cost is that of 64 rows.  Estimates (us a layer) are fits to
+// whole calls of 1 .. 64 streams x 1 .. 256 rows after 0 .. 16,000 positions.
+// Two layers of 2,048 columns, row kernel / MFMA, ms: after 16,000 positions 64 x
+// 1 rows 1.77 / 3.66, 64 x 2 2.66 / 3.69, 64 x 4 4.03 / 3.83, 64 x 8 6.88 / 3.99,
+// 32 x 2 1.39 / 1.67, 32 x 6 2.85 / 1.74, 1 x 48 0.95 / 0.87; after 1,000 64 x 1
+// 1.04 / 1.15, 64 x 2 1.29 / 1.17, 16 x 6 0.59 / 0.45; 32 prompts of about 99 rows
+// 720 / 31 us a layer.  Eight heads per kv head: MFMA at every point (64 x 2 rows
+// 5.10 / 2.30 after 4,000, 1.83 / 1.30 without any).
+static bool packed_one_group(int n_items, int hkv);
+bool flash_packed_wins(const PackedRows& p, int G, int hkv) {
+  if ((long long)p.rows * hkv < 384) return false;
+  if (G == 8) return true;
+  const double rows_us = hkv * (0.028 * p.rows + 4.25e-5 * p.row_keys);
+  const double per_item = packed_one_group(p.items, hkv) ? 1.86e-4 : 1.3e-4;
+  const double items_us = std::max(hkv * per_item * p.item_keys, 0.0156 * p.longest);
+  return items_us <= rows_us;
+}
+
 // One key-split group (256 threads, three workgroups a CU) once the launch has
 // three workgroups per CU, two below: fewer, longer chains while the chip is
 // full, shorter ones while it is not.  Measured per layer, one / two / four
@@ -425,12 +448,13 @@ void flash_prefill(hipStream_t st, const _Float16* qM, const _Float16* kv, KvLay
 // 256 (2,048) 78 / 95 / 148 us; a prefill call of 8 x 64 rows after 512
 // positions (128 workgroups) 3.11 / 2.89 / 3.02 ms, of 2 x 64 rows after 8,000
 // 5.91 / 4.08 / 4.38 ms.
+static bool packed_one_group(int n_items, int hkv) { return (long long)n_items * hkv * 2 >= 3 * 256; }
 void flash_prefill_packed(hipStream_t st, const float* q, const _Float16* kv, KvLayout L, int layer,
                           const int* page_table, const FlashItem* items, int n_items, int hq, int hkv, _Float16* oM) {
   const dim3 grid(n_items, hkv, 2);
   if (hq / hkv == 8)
     launch_flash<8, 1, true>(st, grid, nullptr, q, kv, L, layer, page_table, items, 0, 0, 0, hq, oM);
-  else if ((long long)n_items * hkv * 2 >= 3 * 256)
+  else if (packed_one_group(n_items, hkv))
     launch_flash<4, 1, true>(st, grid, nullptr, q, kv, L, layer, page_table, items, 0, 0, 0, hq, oM);
   else
     launch_flash<4, 2, true>(st, grid, nullptr, q, kv, L, layer, page_table, items, 0, 0, 0, hq, oM);

@@ -781,26 +781,30 @@ hh_status do_prefill_batch(hh_ctx* c, int n, const int32_t* ids, const int32_t* 
       }
     }
     const int R = (int)rs.size(), ne = (int)last_r.size();
-    // fp16 caches: MFMA attention over each stream's rows once the row kernel
-    // would have 1.5 workgroups per CU (32 prompts of about 99 rows: 720 ->
-    // 31 us a layer, 32 of 256: 2,100 -> 78 us).  Its chain over a stream's
-    // keys is longer, so few rows on long contexts stay with the row kernel
-    // (whole calls, row kernel / MFMA: 2 x 8 rows after 2,000 positions 1.35 /
-    // 1.55 ms, after 8,000 2.41 / 3.04 ms; 8 x 8 after 2,000 2.18 / 1.93 ms;
-    // 2 x 64 after 8,000 7.36 / 4.08 ms).
+    // fp16 caches: MFMA attention over each stream's rows where it is the
+    // faster one (flash_packed_wins).
     std::vector<FlashItem> items;
-    if (sizeof(TKV) == 2 && (long long)R * g.n_kv_heads >= 384 &&
+    if (sizeof(TKV) == 2 &&
         flash_prefill_supported(g.n_heads / g.n_kv_heads, g.max_context,
                                 (size_t)L.n_pages * 2 * g.n_kv_heads * kPage * kHeadDim)) {
+      PackedRows pr;
       for (int r = 0; r < R;) {
         int e = r + 1;
         while (e < R && rs[e] == rs[r]) ++e;
-        const int pairs = ((e - r + 31) / 32 + 1) / 2;
+        const int pairs = ((e - r + 31) / 32 + 1) / 2, keys = rp[e - 1] + 1;
         for (int k = 0; k < pairs; ++k) items.push_back(FlashItem{rs[r], rp[r], r, e - r, k});
+        pr.rows += e - r;
+        pr.items += pairs;
+        pr.row_keys += (double)(e - r) * keys;
+        pr.item_keys += (double)pairs * keys;
+        pr.longest = std::max(pr.longest, keys);
         r = e;
       }
-      HIPCHK(c, hipMemcpyAsync(c->at<FlashItem>(L.items), items.data(), items.size() * sizeof(FlashItem),
-                               hipMemcpyHostToDevice, st));
+      if (flash_packed_wins(pr, g.n_heads / g.n_kv_heads, g.n_kv_heads))
+        HIPCHK(c, hipMemcpyAsync(c->at<FlashItem>(L.items), items.data(), items.size() * sizeof(FlashItem),
+                                 hipMemcpyHostToDevice, st));
+      else
+        items.clear();
     }
     HIPCHK(c, hipMemcpyAsync(row_stream, rs.data(), R * sizeof(int), hipMemcpyHostToDevice, st));
     HIPCHK(c, hipMemcpyAsync(row_pos, rp.data(), R * sizeof(int), hipMemcpyHostToDevice, st));

@@ -19,7 +19,8 @@ def shape(hkv):
 
 # Four heads per kv head run two key-split groups below 768 workgroups (4 per
 # item here) and one from there on; eight heads always one.  Fewer than
-# 192 rows (two kv heads) or 384 (one) stay with the row kernel.
+# 192 rows (two kv heads) or 384 (one) stay with the row kernel, and so do
+# streams of few rows each on longer contexts.
 EDGES = [1, 31, 32, 33, 63, 64, 65, 100]
 CASES = {
     "edges": (2, EDGES, 0, 0),
@@ -28,6 +29,7 @@ CASES = {
     "below the row threshold": (2, [95, 96], 0, 0),
     "at the row threshold": (2, [95, 97], 0, 0),
     "one group": (2, [1 + (17 * i) % 70 for i in range(190)], 3, 0),
+    "few rows a stream": (2, [1] * 195, 260, 0),
     "eight heads": (1, EDGES, 2, 0),
 }
 
