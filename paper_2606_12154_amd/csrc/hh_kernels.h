@@ -88,7 +88,7 @@ struct RowNorm {
 struct WTiles {
   const _Float16* h = nullptr;
   const unsigned char* q = nullptr;  // codes: 1 KiB per 16 rows x 128 k
-  const _Float16* s = nullptr;       // scales (times 2^s), see tile_q4
+  const _Float16* s = nullptr;       // scales (times 16 wscale), see tile_q4
   bool by_k = false;                 // scales belong to k (W_down), not to rows
 };
 
@@ -251,7 +251,7 @@ void tile16(hipStream_t st, const _Float16* src, _Float16* dst, int rows, int K,
 // codes: chunk (rb (K / 128) + b) 64 + l (16 bytes) holds row 16 rb + l % 16,
 // k 128 b + 32 j + 8 (l / 16) .. + 8 in dword j, element 2 p in nibble p and
 // 2 p + 1 in nibble p + 4; rows past the matrix hold zeros (code 8);
-// scales: 4 halfs (s * scale) of the row's groups 4 b .. + 4 at index
+// scales: 4 halfs (16 s * scale) of the row's groups 4 b .. + 4 at index
 // ((rb (K / 128) + b) 16 + row % 16) 4.
 // by_k: src holds the rows of the transpose (K of them, rows / 2 + rows / 16
 // bytes, groups along the logical rows, a multiple of 32): the scale of (row n,

@@ -1681,25 +1681,28 @@ static bool launch_skinny_res(hipStream_t st, const _Float16* A, int M, const _F
 // The activation-resident product on a 4-bit model's stored codes: lockstep
 // decoding streamed the fp16 copies of the dequantized values, 3.6 times the
 // bytes.  A lane's 16-byte load holds its operand rows' codes of four K
-// blocks; a block's eight codes become fp16 values of exactly q (nibbles in the
-// mantissa of 1024, then minus 1032) times the group's scale, the same fp16
-// operand as the copy's.  us at 6 rows of the 1B model, fp16 tiles / codes: gate/up
-// 14.5 / 8.8, down 11.4 / 9.0, O 7.2 / 7.1, QKV 5.0 / 4.6, LM head 86 / 35; what is
-// left is a launch's start and end and the activations' round trip, and in
-// the head the unpacking (15 instructions per 8 codes and lane).
+// blocks; a block's eight codes become fp16 values of exactly q / 16 (nibbles in
+// the mantissa of 64, then minus 64.5) times the group's scale (times 16: at most
+// 16 2^14 / 7).  Both factors are exact and the product is rounded once, so it is
+// the copy's operand, down to scales of 2^-21 (2^-35 of the model's largest
+// weight; below, the scale is rounded too).  us at 6 rows of the 1B model, fp16
+// tiles / codes: gate/up 14.5 / 8.8, down 11.4 / 9.0, O 7.2 / 7.1, QKV 5.0 / 4.6, LM
+// head 86 / 35; what is left is a launch's start and end and the activations'
+// round trip, and in the head the unpacking (15 instructions per 8 codes and
+// lane).
 // Waves, K groups, activations and the tail are k_gemm_skinny_res's.  BY_K:
 // scales belong to k (W_down, grouped along its output rows) and go through
 // LDS.  LOOP (LM head): a workgroup walks the column blocks with its
 // activations resident and the next block's codes in flight.
-// mask and magic: 0x000F000F and 0x64006400, in registers (q4_constants), so that
+// mask and magic: 0x000F000F and 0x54005400, in registers (q4_constants), so that
 // each pair takes one and-or instruction, which has no room for literals.
 __device__ __forceinline__ void q4_constants(unsigned& mask, unsigned& magic) {
   asm("s_mov_b32 %0, 0x000f000f" : "=s"(mask));
-  asm("v_mov_b32 %0, 0x64006400" : "=v"(magic));
+  asm("v_mov_b32 %0, 0x54005400" : "=v"(magic));
 }
 __device__ __forceinline__ f16x8 q4_values(unsigned w, unsigned mask, unsigned magic) {
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  const h2 off = {(_Float16)1032.f, (_Float16)1032.f};
+  const h2 off = {(_Float16)64.5f, (_Float16)64.5f};
   f16x8 r;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {

@@ -231,7 +231,7 @@ __global__ void k_tile_q4(const unsigned char* __restrict__ src, unsigned char* 
     v[j] = w;
   }
   reinterpret_cast<u32x4*>(codes)[i] = v;
-  auto stored = [&](size_t at) { return (_Float16)((float)*reinterpret_cast<const __bf16*>(src + at) * scale); };
+  auto stored = [&](size_t at) { return (_Float16)((float)*reinterpret_cast<const __bf16*>(src + at) * (16.f * scale)); };
   if (!by_k) {
     if (l < 16)
 #pragma unroll

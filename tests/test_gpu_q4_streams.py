@@ -49,3 +49,32 @@ def test_lockstep_rows(model, n):
         worst = max(worst, check_logits(lg, dec.decode_batch(caches, feed), TOL, what=f"{name}, {n} rows, step {step}"))
         assert (tok == np.argmax(lg, -1)).all()
     print(f"{name}, {n} rows: max-abs {worst:.4g}")
+
+
+def test_small_scales():
+    """A head whose scales are 2^-19 .. 2^-17 in the fp16 operands' units (the
+    embedding sets the unit): 32 rows multiply its codes, 64 rows the fp16
+    copy of its values, so the same operands give the same errors but for the
+    order of sums.  Scales rounded before the product gave 4 times the error."""
+    sh = synth.ModelShape(1, 256, 4, 2, 64, 128, 1000, 1e-5, 1e4, False, synth.BF16)
+    rng = np.random.default_rng(5)
+    tensors = synth.make_weights(sh, 52)
+    for i, (name, shp) in enumerate(sh.tensor_specs()):
+        std = {"embed": 2.0 ** 10, "l0.wo": 0.0, "l0.w_down": 0.0, "lm_head": 2.0 ** -17}.get(name)
+        if std is not None:
+            tensors[i] = synth.f32_to_bf16_bits((std * rng.standard_normal(shp)).astype(np.float32))
+    w = oracle.q4_model_weights(sh, synth.weights_as_f64(sh, tensors))
+    toks = synth.make_tokens(sh.vocab, 64, 6)
+    x = w["embed"][toks]
+    ref = x / np.sqrt((x * x).mean(-1, keepdims=True) + sh.rms_eps) @ w["lm_head"].T
+    ctx = hh.Context(hh.make_config(sh, 2, 80, 80, weight_format=hh.HH_WF_Q4G32))
+    try:
+        ctx.load_weights(tensors)
+        _, copy = ctx.prefill(0, toks, logits="all")
+        ctx.reset()
+        _, codes = ctx.prefill(0, toks[:32], logits="all")
+    finally:
+        ctx.close()
+    e_copy, e_codes = (float(np.linalg.norm(g[:32] - ref[:32]) / np.linalg.norm(ref[:32])) for g in (copy, codes))
+    print(f"error of the copy {e_copy:.3g}, of the codes {e_codes:.3g}")
+    assert e_codes <= 1.05 * e_copy
