@@ -253,8 +253,7 @@ struct EpiGateUp {
     return j < F ? (c < half ? j : F + j) : -1;
   }
   // Register epilogue (half == 32): gate columns cb + 8 h .. + 8, their up
-  // columns 32 later.  SiLU with the hardware reciprocal (the result is
-  // rounded to fp16 right after, far coarser than its 1-ulp error).
+  // columns 32 later.
   template <int FM>
   __device__ void tile(int row0, int cb, int h, int M, const f32x4 (&acc)[FM][4]) const {
     const int col = (cb / 64) * 32 + 8 * h;
@@ -265,7 +264,7 @@ struct EpiGateUp {
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float gt = acc[i][e >> 2][e & 3] * scale;
-        o[e] = (_Float16)(gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * (acc[i][2 + (e >> 2)][e & 3] * scale));
+        o[e] = (_Float16)(silu_rcp(gt) * (acc[i][2 + (e >> 2)][e & 3] * scale));
       }
       const int row = row0 + 16 * i;
       if (row < M) *reinterpret_cast<f16x8*>(m + (size_t)row * F + col) = o;
