@@ -50,8 +50,9 @@ void finalize(hipStream_t st, int r0, int n, const int* row_stream, const int* r
 constexpr int kPutInts = 62;
 void put_ints(hipStream_t st, int* dst, const int* src, int n);
 // Position, pending token and argmax slot of streams [s0, s0 + n) to zero,
-// and the decode-step error word (when given).
-void reset_streams(hipStream_t st, int s0, int n, int* pos, int* pending, unsigned long long* slot, int* err);
+// and the decode-step error word (when given).  Returns the launch's own
+// status: the thread's last error may be another library's.
+hipError_t reset_streams(hipStream_t st, int s0, int n, int* pos, int* pending, unsigned long long* slot, int* err);
 
 // fp32 scratch (in the context's arena) for split-K partial tiles of the
 // MFMA GEMM; splits are reduced until the partials fit.

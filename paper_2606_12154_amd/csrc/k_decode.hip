@@ -911,8 +911,9 @@ __global__ void k_reset_streams(int s0, int n, int* __restrict__ pos, int* __res
   if (i == 0 && err) *err = 0;
 }
 
-void reset_streams(hipStream_t st, int s0, int n, int* pos, int* pending, unsigned long long* slot, int* err) {
-  k_reset_streams<<<(n + 63) / 64, 64, 0, st>>>(s0, n, pos, pending, slot, err);
+hipError_t reset_streams(hipStream_t st, int s0, int n, int* pos, int* pending, unsigned long long* slot, int* err) {
+  void* args[] = {&s0, &n, &pos, &pending, &slot, &err};
+  return hipLaunchKernel(reinterpret_cast<const void*>(k_reset_streams), dim3((n + 63) / 64), dim3(64), args, 0, st);
 }
 
 void finalize(hipStream_t st, int r0, int n, const int* row_stream, const int* row_pos, unsigned long long* slot,

@@ -930,9 +930,8 @@ hh_status reset_range(hh_ctx* c, int s0, int n, bool clear_error) {
     c->len[s] = 0;
   }
   int* err = clear_error && c->step_wg > 0 ? reinterpret_cast<int*>(c->at<unsigned long long>(c->L.ll) + c->L.ll_words - 8) : nullptr;
-  reset_streams(c->stream, s0, n, c->at<int>(c->L.pos), c->at<int>(c->L.pending),
-                c->at<unsigned long long>(c->L.slot), err);
-  HIPCHK(c, hipGetLastError());
+  HIPCHK(c, reset_streams(c->stream, s0, n, c->at<int>(c->L.pos), c->at<int>(c->L.pending),
+                          c->at<unsigned long long>(c->L.slot), err));
   return HH_OK;
 }
 

@@ -244,6 +244,25 @@ def test_reset_and_errors(tiny):
     check_logits(got, ref, TOL, what="after reset")
 
 
+def test_reset_with_another_librarys_error_pending(tiny):
+    """A HIP call of the program's own that failed leaves its error on the
+    thread; a reset reports its own launch, not that."""
+    import ctypes
+    shape, tensors, _ = tiny
+    ctx = new_context(shape, tensors, streams=2)
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    hip.hipGetLastError.restype = ctypes.c_int
+    try:
+        assert hip.hipSetDevice(1 << 20) != 0
+        ctx.reset(0)
+        assert hip.hipGetLastError() != 0  # still the program's to read
+    finally:
+        hip.hipGetLastError()
+        ctx.close()
+
+
 def test_stale_arena_contents(tiny):
     """The arena is caller memory with arbitrary contents: KV slots past a
     stream's length (the rest of its last page) must not leak into the
