@@ -84,14 +84,19 @@ struct RowNorm {
   float* ss_out = nullptr;
 };
 
-// A matrix laid out for the <= 32-row GEMMs: fp16 operand tiles (tile16), and
-// for 4-bit models the codes themselves (tile_q4).  Null: not kept.
+// A matrix laid out for the <= 32-row GEMMs: fp16 operand tiles (tile16), or
+// for 4-bit models the codes themselves (tile_q4), or both where the codes serve
+// not every product (skinny_codes_serve).  Null: not kept.
 struct WTiles {
   const _Float16* h = nullptr;
   const unsigned char* q = nullptr;  // codes: 1 KiB per 16 rows x 128 k
   const _Float16* s = nullptr;       // scales (times 16 wscale), see tile_q4
   bool by_k = false;                 // scales belong to k (W_down), not to rows
 };
+
+// Whether the codes serve every product of at most min(32, max_rows) rows with
+// this matrix (head: the LM head's; ws_bytes: the workspace for split partials).
+bool skinny_codes_serve(int K, int n_cols, bool head, bool by_k, size_t ws_bytes, int max_rows);
 
 template <typename TM, typename TKV>
 struct GemmKernels {

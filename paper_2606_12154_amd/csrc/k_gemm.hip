@@ -1878,20 +1878,51 @@ static bool skinny_q4_go(hipStream_t st, int grid, const _Float16* A, int M, con
                 : skinny_q4_run<Epi, NB4, KW, BY_K, LOOP, false>(st, grid, A, M, wt, K, nb, per, part, n_cols, e, rn);
 }
 
-// Shapes: K a multiple of 128, at most 1,024 of it per K group, one workgroup
-// per (64 columns, split) up to two per CU, or the LM head, which loops.
+// K splits of the <= 32-row kernels, 32-wide K blocks per split, and K groups
+// per workgroup.
+struct SkinnyPlan {
+  int splits, per, kw;
+};
+static SkinnyPlan skinny_plan(int M, int K, int n_cols, size_t ws_bytes, bool codes) {
+  const int nb = (n_cols + 63) / 64, nk = K / 32;
+  // Split K only to give about 256 workgroups, with at least 16 K blocks
+  // (512 K) per split: at 32 rows the O and QKV products (64 K blocks) run
+  // 4 splits, not 8 and 6 (step 1.002 -> 0.978 ms; the down projection keeps
+  // 8, which 4 slowed).
+  int splits = std::max(1, std::min((256 + nb - 1) / nb, nk / 16));
+  while (splits > 1 && (size_t)splits * M * n_cols * sizeof(float) > ws_bytes) --splits;
+  int per = (nk + splits - 1) / splits;
+  if (codes) per = (per + 3) & ~3;  // whole 128-wide blocks of codes
+  splits = (nk + per - 1) / per;
+  // Unsplit (long) K ranges take two K groups per workgroup: eight waves per
+  // CU keep more weight loads in flight (gate/up 17.0 -> 15.9 us at 32 rows).
+  return SkinnyPlan{splits, per, splits == 1 ? 2 : 1};
+}
+
+// Shapes of the kernel on codes: K a multiple of 128, at most 1,024 of it per K
+// group, one workgroup per (64 columns, split) up to two per CU, or the LM head,
+// which loops and does not split.  (31-bit byte offsets as in launch_skinny.)
+static bool skinny_q4_fits(const SkinnyPlan& p, int K, int n_cols, bool head, bool by_k) {
+  const int nb = (n_cols + 63) / 64;
+  if (K % 128 || p.per % 4 || (p.per / 4 + p.kw - 1) / p.kw > 8) return false;
+  if ((size_t)((n_cols + 15) / 16) * 16 * K * 2 >= ((size_t)1 << 31) || (by_k && n_cols % 64)) return false;
+  return head ? p.splits == 1 && !by_k : (long long)nb * p.splits <= 2 * 256;
+}
+bool skinny_codes_serve(int K, int n_cols, bool head, bool by_k, size_t ws_bytes, int max_rows) {
+  for (int M = 1; M <= std::min(32, max_rows); ++M)
+    if (!skinny_q4_fits(skinny_plan(M, K, n_cols, ws_bytes, true), K, n_cols, head, by_k)) return false;
+  return true;
+}
+
 template <class Epi>
 static bool launch_skinny_q4(hipStream_t st, const _Float16* A, int M, const WTiles& wt, int K, int nb, int splits,
                              int per32, float* part, int n_cols, int kw, const Epi& e, const RowNorm& rn) {
   constexpr bool head = std::is_same<Epi, EpiLogits<false>>::value;
+  if (!wt.q || !skinny_q4_fits(SkinnyPlan{splits, per32, kw}, K, n_cols, head, wt.by_k)) return false;
   const int per = per32 / 4, g = (per + kw - 1) / kw;
-  if (!wt.q || K % 128 || per32 % 4 || g > 8) return false;
-  if ((size_t)((n_cols + 15) / 16) * 16 * K / 2 >= ((size_t)1 << 31) || (wt.by_k && n_cols % 64)) return false;
   if constexpr (head) {
-    if (splits != 1 || kw != 2 || wt.by_k) return false;
     return skinny_q4_go<Epi, 8, 2, false, true>(st, std::min(nb, 256), A, M, wt, K, nb, per, part, n_cols, e, rn);
   } else {
-    if ((long long)nb * splits > 2 * 256) return false;
     auto go = [&](auto n, auto k, auto by) {
       return skinny_q4_go<Epi, decltype(n)::value, decltype(k)::value, decltype(by)::value, false>(
           st, nb * splits, A, M, wt, K, nb, per, part, n_cols, e, rn);
@@ -1925,29 +1956,20 @@ static int launch_skinny(hipStream_t st, GemmWorkspace ws, const _Float16* A, in
   // The consumer half reads at most 32 block sums per row (a multiple of 4).
   if (rn.ss_in && (rn.nss > 32 || rn.nss % 4)) return 0;
   const int nb = (n_cols + 63) / 64;
-  const int nk = K / 32;
-  // Split K only to give about 256 workgroups, with at least 16 K blocks
-  // (512 K) per split: at 32 rows the O and QKV products (64 K blocks) run
-  // 4 splits, not 8 and 6 (step 1.002 -> 0.978 ms; the down projection keeps
-  // 8, which 4 slowed).
-  int splits = std::max(1, std::min((256 + nb - 1) / nb, nk / 16));
-  while (splits > 1 && (size_t)splits * M * n_cols * sizeof(float) > ws.bytes) --splits;
-  int per = (nk + splits - 1) / splits;
-  if (wt.q) per = (per + 3) & ~3;  // whole 128-wide blocks of codes
-  splits = (nk + per - 1) / per;
+  const SkinnyPlan plan = skinny_plan(M, K, n_cols, ws.bytes, wt.q != nullptr);
+  const int splits = plan.splits, per = plan.per, kw = plan.kw;
   const _Float16* Wt = wt.h;
   float* part = splits > 1 ? ws.ptr : nullptr;
   if (!(std::is_same<Epi, EpiResid>::value && splits > 1 && n_cols % 64 == 0 && nb <= rn.ncnt)) rn.cnt = nullptr;
-  // Unsplit (long) K ranges take two K groups per workgroup: eight waves per
-  // CU keep more weight loads in flight (gate/up 17.0 -> 15.9 us at 32 rows).
-  const int kw = splits == 1 ? 2 : 1;
-  if (!launch_skinny_q4<Epi>(st, A, M, wt, K, nb, splits, per, part, n_cols, kw, e, rn) &&
-      !launch_skinny_res<Epi>(st, A, M, Wt, K, nb, splits, per, part, n_cols, kw, e, rn)) {
-    rn.cnt = nullptr;
-    if (kw == 2)
-      k_gemm_skinny<Epi, 8, 2><<<nb * splits, 512, 0, st>>>(A, M, Wt, K, nb, per, part, n_cols, e, rn);
-    else
-      k_gemm_skinny<Epi, 8, 1><<<nb * splits, 256, 0, st>>>(A, M, Wt, K, nb, per, part, n_cols, e, rn);
+  if (!launch_skinny_q4<Epi>(st, A, M, wt, K, nb, splits, per, part, n_cols, kw, e, rn)) {
+    if (!Wt) return 0;
+    if (!launch_skinny_res<Epi>(st, A, M, Wt, K, nb, splits, per, part, n_cols, kw, e, rn)) {
+      rn.cnt = nullptr;
+      if (kw == 2)
+        k_gemm_skinny<Epi, 8, 2><<<nb * splits, 512, 0, st>>>(A, M, Wt, K, nb, per, part, n_cols, e, rn);
+      else
+        k_gemm_skinny<Epi, 8, 1><<<nb * splits, 256, 0, st>>>(A, M, Wt, K, nb, per, part, n_cols, e, rn);
+    }
   }
   if (rn.cnt) {
     if (fused) *fused = 1;
@@ -2088,7 +2110,7 @@ static int run_gemm(hipStream_t st, GemmWorkspace ws, const TM* A, int M, const 
                     int* fused = nullptr) {
   if (fused) *fused = 0;
   if constexpr (sizeof(TM) == 2) {
-    if (M <= 32 && Wt.h && K % 64 == 0) {
+    if (M <= 32 && (Wt.h || Wt.q) && K % 64 == 0) {
       const int sp = launch_skinny(st, ws, reinterpret_cast<const _Float16*>(A), M, Wt, K, n_cols, e, defer, rn, fused);
       if (sp > 0) return sp;
     }

@@ -31,6 +31,8 @@ constexpr int kMaxStepWG = 1024; // upper bound on persistent decode-step workgr
 
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
+constexpr size_t kNoTiles = ~size_t(0);
+
 struct Layout {
   // element sizes
   size_t ew, ekv, em;
@@ -39,7 +41,9 @@ struct Layout {
   size_t embed, lm_head, embedM, lm_headM;
   std::vector<size_t> wqkv, wo, wgu, wdown, wdownT, wqkvM, woM, wguM, wdownM, attn_norm, mlp_norm;
   // 16 x 32 operand tiles of the fp16 copies for <= 32-row GEMMs (multi-stream
-  // contexts of bf16 models only; empty otherwise).
+  // contexts of bf16 models only; empty otherwise, kNoTiles where 4-bit codes
+  // serve the matrix); tiled: such a context, with layers.
+  bool tiled;
   std::vector<size_t> wqkvT16, woT16, wguT16, wdownT16;
   size_t lm_headT16;
   // Stored 4-bit rows (HH_WF_Q4G32 only; empty otherwise): [Wq; Wk; Wv],
@@ -125,6 +129,12 @@ Layout make_layout(const hh_config& c) {
   const int mp = c.max_prefill > 0 ? std::min(c.max_prefill, c.max_context) : c.max_context;
   L.rows_cap = std::max(c.max_streams, mp);
   L.logit_rows = std::max(c.max_streams, kLogitRows);
+  // Split-K partials: up to 4 splits of the widest non-head product at R rows, at most 256 MiB.
+  const size_t R = L.rows_cap, tm = bf ? 2 : 4;
+  L.gemm_ws_bytes = std::min<size_t>((size_t)4 * R * std::max((size_t)2 * F, (size_t)L.nqkv) * 4, (size_t)256 << 20);
+  // 4-bit models: codes as operand tiles for the <= 32-row GEMMs.
+  const bool codes = c.weight_format == HH_WF_Q4G32 && c.max_streams > 1 && c.n_layers > 0 && d % 128 == 0 &&
+                     F % 128 == 0 && hq * 64 % 128 == 0;
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off += al(bytes); return o; };
   L.embed = take(V * d * L.ew);
@@ -146,13 +156,18 @@ Layout make_layout(const hh_config& c) {
       L.wdownM.push_back(take(d * F * L.em));
     }
     if (c.max_streams > 1) {
-      auto tiles = [&](size_t logical_rows, size_t K) { return take((logical_rows + 15) / 16 * 16 * K * 2); };
-      L.lm_headT16 = tiles(V, d);
+      // fp16 operand tiles, but where a 4-bit model's codes serve every product.
+      auto tiles = [&](size_t rows, size_t K, bool head = false, bool by_k = false) {
+        if (codes && skinny_codes_serve((int)K, (int)rows, head, by_k, L.gemm_ws_bytes, L.rows_cap)) return kNoTiles;
+        return take((rows + 15) / 16 * 16 * K * 2);
+      };
+      L.tiled = c.n_layers > 0;
+      L.lm_headT16 = tiles(V, d, true);
       for (int l = 0; l < c.n_layers; ++l) {
         L.wqkvT16.push_back(tiles(L.nqkv, d));
         L.woT16.push_back(tiles(d, hq * 64));
         L.wguT16.push_back(tiles((F + 31) / 32 * 64, d));
-        L.wdownT16.push_back(tiles(d, F));
+        L.wdownT16.push_back(tiles(d, F, false, true));
       }
     }
   } else {
@@ -172,7 +187,7 @@ Layout make_layout(const hh_config& c) {
       L.wguQ.push_back(q4(2 * F, d));
       L.wdownTQ.push_back(q4(F, d));
     }
-    if (c.max_streams > 1 && d % 128 == 0 && F % 128 == 0 && hq * 64 % 128 == 0) {
+    if (codes) {
       auto tiles4 = [&](size_t rows, size_t K) { return take(q4_tile_codes(rows, K) + (rows + 15) / 16 * 16 * (K / 32) * 2); };
       L.lm_headT4 = tiles4(V, d);
       for (int l = 0; l < c.n_layers; ++l) {
@@ -206,7 +221,6 @@ Layout make_layout(const hh_config& c) {
   // One counter per 64-column block of a residual product.
   L.nrm_ncnt = (int)(d / 64 + 1);
   L.nrm_cnt = take((size_t)L.nrm_ncnt * 4);
-  const size_t R = L.rows_cap, tm = bf ? 2 : 4;
   L.row_stream = take(R * 4);
   L.row_pos = take(R * 4);
   L.feed = take(R * 4);
@@ -223,8 +237,6 @@ Layout make_layout(const hh_config& c) {
   L.mM = take(R * F * tm);
   L.part = take((size_t)c.max_streams * hq * kSplitMax * 66 * 4);
   L.logits = take((size_t)L.logit_rows * V * 4);
-  // Split-K partials: up to 4 splits of the widest non-head product at R rows, at most 256 MiB.
-  L.gemm_ws_bytes = std::min<size_t>((size_t)4 * R * std::max((size_t)2 * F, (size_t)L.nqkv) * 4, (size_t)256 << 20);
   L.gemm_ws = take(L.gemm_ws_bytes);
   L.scratch_u32 = take(256);
   // Many-row LM head: the normalised rows as two fp16 terms, and their scales.
@@ -311,7 +323,7 @@ namespace {
 // GEMMs: t16 and t4 are its offsets (t4: nullptr when not kept).
 WTiles tiles_at(const hh_ctx* c, size_t t16, const size_t* t4, size_t rows, size_t K, bool by_k) {
   WTiles t;
-  t.h = c->at<_Float16>(t16);
+  if (t16 != kNoTiles) t.h = c->at<_Float16>(t16);
   if (t4) {
     t.q = c->at<unsigned char>(*t4);
     t.s = c->at<_Float16>(*t4 + q4_tile_codes(rows, K));
@@ -321,7 +333,7 @@ WTiles tiles_at(const hh_ctx* c, size_t t16, const size_t* t4, size_t rows, size
 }
 WTiles head_tiles(const hh_ctx* c) {
   const Layout& L = c->L;
-  if (L.wqkvT16.empty()) return WTiles();
+  if (!L.tiled) return WTiles();
   return tiles_at(c, L.lm_headT16, L.wqkvT4.empty() ? nullptr : &L.lm_headT4, c->cfg.vocab, c->cfg.d_model, false);
 }
 
@@ -361,7 +373,7 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
   // squares are in nrm_ss, not yet applied.  (For prompt rows the large-tile
   // kernels' arrival chain cost as much as the norm pass it replaced.)
   const bool rnorm = sizeof(TM) == 2 && !decode_gemv && prefill_stream < 0 && head_row == -1 &&
-                     !L.wqkvT16.empty() && GK::norm_fusable(d) && d % 256 == 0 && d <= 2048 && c->row_norm;
+                     L.tiled && GK::norm_fusable(d) && d % 256 == 0 && d <= 2048 && c->row_norm;
   float* nss = rnorm ? c->at<float>(L.nrm_ss) : nullptr;
   int* ncnt = rnorm ? c->at<int>(L.nrm_cnt) : nullptr;
   RowNorm rn_use;
@@ -393,7 +405,7 @@ void enqueue_layers(hh_ctx* c, int n, bool decode_gemv, int s_max, int head_row,
                          flash_prefill_supported(hq / hkv, c->cfg.max_context,
                                                  (size_t)kl.n_pages * 2 * hkv * kPage * kHeadDim);
       // Flash attention reads only the fp16 queries.
-      const bool tiled = !L.wqkvT16.empty(), t4 = !L.wqkvT4.empty();
+      const bool tiled = L.tiled, t4 = !L.wqkvT4.empty();
       WTiles tq, to, tg, td;
       if (tiled) {
         tq = tiles_at(c, L.wqkvT16[l], t4 ? &L.wqkvT4[l] : nullptr, L.nqkv, d, false);
@@ -1144,14 +1156,17 @@ hh_status hh_load_weights(hh_ctx* c, const void* const* tensors, int32_t n_tenso
       for (int l = 0; l < g.n_layers; ++l)
         transpose(st, c->at<_Float16>(L.wdownM[l]), c->at<_Float16>(L.wdownT[l]), (int)d, (int)F);
     }
-    if (!L.wqkvT16.empty()) {
-      tile16(st, c->at<_Float16>(L.lm_headM), c->at<_Float16>(L.lm_headT16), (int)V, (int)d, (int)V, 0);
+    if (L.tiled) {
+      auto tiles = [&](size_t src, size_t dst, size_t rows, size_t K, size_t logical, size_t inter) {
+        if (dst != kNoTiles)
+          tile16(st, c->at<_Float16>(src), c->at<_Float16>(dst), (int)rows, (int)K, (int)logical, (int)inter);
+      };
+      tiles(L.lm_headM, L.lm_headT16, V, d, V, 0);
       for (int l = 0; l < g.n_layers; ++l) {
-        tile16(st, c->at<_Float16>(L.wqkvM[l]), c->at<_Float16>(L.wqkvT16[l]), L.nqkv, (int)d, L.nqkv, 0);
-        tile16(st, c->at<_Float16>(L.woM[l]), c->at<_Float16>(L.woT16[l]), (int)d, (int)(hq * 64), (int)d, 0);
-        tile16(st, c->at<_Float16>(L.wguM[l]), c->at<_Float16>(L.wguT16[l]), (int)(2 * F), (int)d,
-               (int)((F + 31) / 32 * 64), (int)F);
-        tile16(st, c->at<_Float16>(L.wdownM[l]), c->at<_Float16>(L.wdownT16[l]), (int)d, (int)F, (int)d, 0);
+        tiles(L.wqkvM[l], L.wqkvT16[l], L.nqkv, d, L.nqkv, 0);
+        tiles(L.woM[l], L.woT16[l], d, hq * 64, d, 0);
+        tiles(L.wguM[l], L.wguT16[l], 2 * F, d, (F + 31) / 32 * 64, F);
+        tiles(L.wdownM[l], L.wdownT16[l], d, F, d, 0);
       }
     }
     if (!L.wqkvT4.empty()) {

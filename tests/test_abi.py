@@ -88,6 +88,23 @@ def test_q4_workspace_adds_the_stored_rows():
     assert expect <= q4 - base <= expect + 256 * (1 + 4 * sh.n_layers)
 
 
+def test_q4_multi_stream_workspace_holds_codes_not_fp16_tiles():
+    # What a second stream adds for the products of at most 32 rows: fp16 operand
+    # tiles of every streamed matrix, or a 4-bit model's codes and scales.
+    sh = synth.ONE_B
+    size = {(f, n): hh.hh_workspace_size(hh.make_config(sh, n, 1024, weight_format=f))
+            for f in (hh.HH_WF_DTYPE, hh.HH_WF_Q4G32) for n in (1, 2)}
+    extra = [size[f, 2] - size[f, 1] for f in (hh.HH_WF_DTYPE, hh.HH_WF_Q4G32)]
+    weights = sh.d_model * (sh.vocab + sh.n_layers * (2 * (sh.q_dim + sh.kv_dim) + 3 * sh.ffn_dim))
+    saved = weights * 2 - weights * 9 // 16
+    assert abs(extra[0] - extra[1] - saved) <= 256 * 2 * (1 + 4 * sh.n_layers)
+    # Where the codes serve not every product (a head that splits K), both stay.
+    odd = synth.ModelShape(2, 1152, 18, 9, 64, 4224, 1001, 1e-5, 1e4, True, synth.BF16)
+    q4 = [hh.hh_workspace_size(hh.make_config(odd, n, 64, weight_format=hh.HH_WF_Q4G32)) for n in (1, 2)]
+    mats = 1152 * (odd.n_layers * (2 * (odd.q_dim + odd.kv_dim) + 3 * odd.ffn_dim) + 1008)
+    assert q4[1] - q4[0] >= mats * 9 // 16 + 1152 * 1008 * 2
+
+
 def test_q4_quantize_rejects_bad_arguments():
     with pytest.raises(hh.HHError) as e:
         hh.hh_q4g32_quantize(1 << 20, 4, 48, 1 << 21, 0)   # K not a multiple of 32
