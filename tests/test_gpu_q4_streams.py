@@ -12,10 +12,17 @@ from paper_2606_12154_amd import hh
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2
-# d 1,152: nine 128-wide K blocks over two K groups; FFN 4,224: 33 blocks in splits
-# of five; a vocabulary that ends inside a block of 64 columns.  d 1,088 and
+# (d, heads, kv heads, FFN, vocabulary).  "whole" and "uneven" split every product's
+# K over workgroups of one K group each: d 1,152 is nine 128-wide K blocks in splits
+# of five and four, FFN 4,224 33 blocks in splits of five; their heads split K too,
+# which leaves them to the fp16 tiles.  Unsplit products have two K groups and the
+# head walks its column blocks: "head" has nine blocks as four and five, gate/up
+# unsplit and 258 head blocks for 256 workgroups, the last one 9 columns wide;
+# "groups" two groups of four blocks in gate/up and a head of 257 whole blocks;
+# "short" splits nothing (five blocks as two and three, down as well).  d 1,088 and
 # FFN 4,160 are no multiples of 128: the fp16 tiles serve those products.
-SHAPES = {"whole": (1024, 16, 4, 4096, 1024), "uneven": (1152, 18, 9, 4224, 1001), "fp16 tiles": (1088, 17, 17, 4160, 1001)}
+SHAPES = {"whole": (1024, 16, 4, 4096, 1024), "uneven": (1152, 18, 9, 4224, 1001), "fp16 tiles": (1088, 17, 17, 4160, 1001),
+          "head": (1152, 18, 9, 8192, 16457), "groups": (1024, 16, 4, 8192, 16448), "short": (640, 10, 5, 640, 1001)}
 
 
 @pytest.fixture(scope="module", params=list(SHAPES))
