@@ -4,6 +4,7 @@ against fp64, at the precision of 32-bit inputs."""
 import numpy as np
 import pytest
 
+import oracle
 import synth
 from gpu_util import new_context
 from paper_2606_12154_amd import hh
@@ -72,3 +73,55 @@ def test_sums(dtype, d, n):
     err = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     print(f"d {d}, {n} rows: {err:.3g}")
     assert err <= 2.0 ** -23
+
+
+def many_tiles(shape, w, toks, tol_of, aligned, **config):
+    """The logits of every row, written by the kernels into the caller's
+    buffer (on a 16-byte boundary or 4 bytes past one, guards on both sides)."""
+    import torch
+    n, vocab, (tensors, embed, head) = len(toks), shape.vocab, w
+    x = embed[toks]
+    h = x / np.sqrt((x * x).mean(-1, keepdims=True) + shape.rms_eps)
+    ref, tol = h @ head.T, tol_of(np.abs(h) @ np.abs(head).T)
+    ctx = hh.Context(hh.make_config(shape, 1, n + 4, **config))
+    try:
+        ctx.load_weights(tensors)
+        first = 4 if aligned else 5
+        buf = torch.full((n * vocab + 16,), 7.0, dtype=torch.float32, device="cuda")
+        out = buf[first:first + n * vocab]
+        nxt = np.zeros(1, dtype=np.int32)
+        torch.cuda.synchronize()
+        hh.hh_prefill(ctx.ctx, 0, toks, hh.HH_LOGITS_ALL, out.data_ptr(), nxt.ctypes.data)
+        got = out.cpu().numpy().reshape(n, vocab)
+        assert bool((buf[:first] == 7.0).all()) and bool((buf[first + n * vocab:] == 7.0).all())
+    finally:
+        ctx.close()
+    assert (np.abs(got - ref) <= tol).all(), float((np.abs(got - ref) / tol).max())
+    assert int(nxt[0]) == int(np.argmax(got[-1]))
+
+
+# More tiles than workgroups, so that each walks several with its loads running
+# ahead: 64 rows take 313 tiles of 128 x 128, 65 rows 313 and 200 rows 626 of
+# 256 x 128; a vocabulary that ends inside a group of 64 columns, with 16-byte rows
+# (stored as such in an aligned buffer) and without.  Tolerance as above.
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("vocab,n", [(40004, 64), (40004, 65), (40004, 200), (40001, 200)])
+def test_many_tiles(vocab, n, aligned):
+    shape = synth.ModelShape(0, 512, 4, 2, 64, 64, vocab, 1e-5, 1e4, True, synth.BF16)
+    tensors = synth.make_weights(shape, 35)
+    embed = synth.weights_as_f64(shape, tensors)["embed"]
+    many_tiles(shape, (tensors, embed, embed), synth.make_tokens(vocab, n, 36), lambda size: 2.0 ** -17 * size, aligned)
+
+
+# 4-bit heads: fp16 rows against the fp16 copy of the values, in the tile kernel
+# from 128 rows on (up to seven weight rows past the head are read with the
+# last columns, and not stored) with the greedy key of the last row only.  A row's
+# values are rounded to fp16, 2^-11 of themselves; sums are 32-bit.
+@pytest.mark.parametrize("aligned", [True, False])
+@pytest.mark.parametrize("vocab,n", [(1003, 127), (1003, 128), (1004, 130), (1001, 597), (40004, 300)])
+def test_four_bit_rows(vocab, n, aligned):
+    shape = synth.ModelShape(0, 512, 4, 2, 64, 64, vocab, 1e-5, 1e4, True, synth.BF16)
+    tensors = synth.make_weights(shape, 37)
+    w = oracle.q4_model_weights(shape, synth.weights_as_f64(shape, tensors))
+    many_tiles(shape, (tensors, w["embed"], w["lm_head"]), synth.make_tokens(vocab, n, 38), lambda size: 1.05 * 2.0 ** -11 * size, aligned,
+               weight_format=hh.HH_WF_Q4G32)
