@@ -2094,7 +2094,6 @@ static int run_tile(hipStream_t st, GemmWorkspace ws, const _Float16* A, int M, 
   const TileCfg c = tile_choice(kind, M, n_cols, K);
   if (c.bm == 256 && c.bn == 256) return launch_tile<256, 256>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
   if (c.bm == 256 && c.bn == 128) return launch_tile<256, 128>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
-  if (c.bm == 128 && c.bn == 256) return launch_tile<128, 256>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
   if (c.bm == 128 && c.bn == 128) return launch_tile<128, 128>(st, ws, A, M, W, K, n_cols, c.splits, e, defer);
   return 0;
 }

@@ -73,9 +73,10 @@ GEMM_KINDS = ("HH_GEMM_QKV", "HH_GEMM_RESID", "HH_GEMM_DOWN", "HH_GEMM_GATEUP")
                                   "256x256x1x8", "256x128x2x8", "128x256x1x8", "128x128x1x8", "128x128x2x8"])
 @pytest.mark.parametrize("n", [256, 200])
 def test_prefill_wide_tiles(one_b, ctx, prompt_ref, tile, n):
-    """Every large-tile GEMM shape (and split-K; four or eight waves per
-    workgroup) of the prompt path, forced for the QKV, residual and gate/up
-    GEMMs, on a whole and a ragged row count."""
+    """Every tile shape (and split-K) of the prompt path, forced for the QKV,
+    residual and gate/up GEMMs, on a whole and a ragged row count.  A shape that
+    the tile kernel does not have (128x256) leaves them to the small-tile
+    kernel; a fourth number is not read."""
     toks, ref = prompt_ref
     saved = {k: os.environ.get(k) for k in GEMM_KINDS}
     try:

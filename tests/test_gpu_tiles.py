@@ -31,7 +31,7 @@ def model(request):
     ctx.close()
 
 
-@pytest.mark.parametrize("tile", ["256x256x1", "256x128x1", "128x256x1", "128x128x1", "128x128x3", "256x256x4"])
+@pytest.mark.parametrize("tile", ["256x256x1", "256x128x1", "256x128x2", "128x128x1", "128x128x3", "256x256x4"])
 @pytest.mark.parametrize("n", [129, 597, ROWS])
 def test_tile_edges(model, tile, n):
     sh, ctx, ref = model
