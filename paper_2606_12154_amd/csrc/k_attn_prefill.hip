@@ -447,7 +447,11 @@ bool flash_packed_wins(const PackedRows& p, int G, int hkv) {
 // groups: 32 prompts of about 99 rows (1,056 workgroups) 31 / 39 / 67 us, 32 of
 // 256 (2,048) 78 / 95 / 148 us; a prefill call of 8 x 64 rows after 512
 // positions (128 workgroups) 3.11 / 2.89 / 3.02 ms, of 2 x 64 rows after 8,000
-// 5.91 / 4.08 / 4.38 ms.
+// 5.91 / 4.08 / 4.38 ms.  Eight heads per kv head (512 threads a group): always
+// one, since two (1,024 threads) leave a wave 128 registers and spill 39.  Whole
+// calls of two layers with four kv heads, one / two groups: 32 x 99 rows 0.94 / 1.02
+// ms, 32 x 256 1.45 / 1.61, 8 x 64 after 512 0.43 / 0.49, 2 x 200 0.30 / 0.35, 2 x
+// 64 after 8,000 0.96 / 0.99; two and eight kv heads alike.
 static bool packed_one_group(int n_items, int hkv) { return (long long)n_items * hkv * 2 >= 3 * 256; }
 void flash_prefill_packed(hipStream_t st, const float* q, const _Float16* kv, KvLayout L, int layer,
                           const int* page_table, const FlashItem* items, int n_items, int hq, int hkv, _Float16* oM) {
