@@ -760,7 +760,7 @@ __global__ __launch_bounds__(256) void k_splitk_finalize(const float* __restrict
 //
 // XCDs: workgroups are dealt round-robin to the eight, and an XCD takes a run
 // of consecutive tiles, numbered down bands of 1,024 rows, so that its 32
-// workgroups share a few row and column tiles in its L2.
+// workgroups share a few row and column tiles in its L2 (but see kDealSplits).
 template <int BM_, int BN_>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, NW = 8, THREADS = 64 * NW;
@@ -779,6 +779,16 @@ typedef __attribute__((address_space(3))) char lds_char;
 __device__ __forceinline__ void buffer_lds16(__amdgpu_buffer_rsrc_t r, lds_char* dst, int voff, unsigned soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff, soff, 0, 0);
 }
+
+// Split products of one round whose units are dealt to the XCDs in turn, columns
+// first, so that an XCD works on every K split of a few column tiles: QKV (us at
+// 256 / 384 rows with the splits of tile_choice 14.6 / 15.3 in runs, 13.2 / 14.0
+// dealt; their partials take as long to write back as the K steps take).  The
+// down projection is no faster dealt (256 rows 17.9 / 18.0, 512 18.6 / 19.0).
+template <class Epi>
+constexpr bool kDealSplits = false;
+template <typename TKV>
+constexpr bool kDealSplits<EpiQKV<TKV>> = true;
 
 template <int BM, int BN, class Epi>
 __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict__ A, int M,
@@ -800,13 +810,20 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
     int m0, n0, split, s0, nk;
   };
   auto unit_at = [&](int idx, Unit& u) {
-    const int o = xcd * per + idx;
+    const bool deal = kDealSplits<Epi> && splits > 1;
+    const int o = deal ? 8 * idx + xcd : xcd * per + idx;
     if (idx >= per || o >= units) return false;
-    constexpr int GM = 1024 / BM;
     u.split = o / tiles;
-    const int t = o - u.split * tiles, band = t / (GM * ntn), r = t - band * GM * ntn, gm = min(GM, ntm - band * GM);
-    u.n0 = (r / gm) * BN;
-    u.m0 = (band * GM + r % gm) * BM;
+    const int t = o - u.split * tiles;
+    if (deal) {
+      u.n0 = (t % ntn) * BN;
+      u.m0 = (t / ntn) * BM;
+    } else {
+      constexpr int GM = 1024 / BM;
+      const int band = t / (GM * ntn), r = t - band * GM * ntn, gm = min(GM, ntm - band * GM);
+      u.n0 = (r / gm) * BN;
+      u.m0 = (band * GM + r % gm) * BM;
+    }
     u.s0 = u.split * steps_per_split;
     u.nk = min(nk_all, u.s0 + steps_per_split) - u.s0;
     return true;
@@ -2077,11 +2094,17 @@ static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
   // Below 512 rows (1B shapes; us a layer at 256 rows, tiles / the small-tile
   // kernel): two or more row tiles of gate/up 26.9 / 33.6; the down
   // projection with K split over 256 workgroups 18.6 / 20.8; QKV from 256 rows
-  // with a 4-way split (its reduction applies the epilogue), 13.6 + 6.6 / 15 + 6;
-  // O stays with the small tiles (13.4 / 8.7: few steps, and two workgroups a
-  // CU hide each other's start).
+  // with the K splits, up to four, that fill one round (its reduction applies the
+  // epilogue): 256 rows, four, 13.2 + 6.3 / 12.8 + 7.0; 384 rows, three, 14.0 +
+  // 8.9 / 24.0 (four, two rounds, 17.7 + 8.2); 448 rows, two, 15.3 + 8.9 (four
+  // 18.0 + 9.0); O stays with the small tiles (13.4 / 8.7: few steps, and two
+  // workgroups a CU hide each other's start).
   if (kind == GemmKind::GateUp && (n_cols < 8192 || M <= 128)) return TileCfg{0, 0, 1};
-  if (kind == GemmKind::QKV && M < 512) return M >= 256 ? TileCfg{128, 128, 4} : TileCfg{0, 0, 1};
+  if (kind == GemmKind::QKV && M < 512) {
+    if (M < 256) return TileCfg{0, 0, 1};
+    const int tiles = (M + 127) / 128 * ((n_cols + 127) / 128);
+    return TileCfg{128, 128, std::max(1, std::min(4, 256 / tiles))};
+  }
   if (kind == GemmKind::Resid && M < 512 && (K < 4096 || M <= 128)) return TileCfg{0, 0, 1};
   return fit_tile(kind, M, n_cols, K, kind == GemmKind::Resid ? 8 : 1);
 }
