@@ -674,8 +674,18 @@ void enqueue_head_rows(hh_ctx* c, int r0, int n, float* logits, unsigned long lo
     // The shared pass costs as much for one row as for 32, the one-row head its
     // own pass over the weights for each (1B head, calls of one / two / three
     // rows: bf16 159 / 246 / 330 us against 195 .. 205, fp32 316 / 473 / 630
-    // against 550).
-    if (n <= (sizeof(TM) == 2 ? 1 : 2)) {
+    // against 550).  bf16 shares from two rows on (smaller heads too: 1,024 x
+    // 32,000, two rows, 263 against 240 us a call).  In fp32 the shared pass is 32-wide
+    // K steps of one buffer, each the longer the more 64-column blocks a CU has,
+    // so the rows at which it wins depend on the head: three for the 1B head,
+    // four for 512 x 50,000 and 256 x 4,096, five for 1,024 x 32,000 (a row 25 us,
+    // the pass 122).
+    int one_row = 1;
+    if (sizeof(TM) != 2) {
+      const double v = g.vocab, row_us = 5.0 + 4.0 * d * v / 6.7e6;
+      one_row = (int)((5.0 + d / 32.0 * (2.3 + 0.5 * v / (64 * 256))) / row_us);
+    }
+    if (n <= one_row) {
       for (int i = 0; i < n; ++i)
         enqueue_head_row<TW, TKV, TM>(c, r0 + i, logits + (size_t)i * g.vocab, i + 1 == n ? slot : nullptr);
       return;

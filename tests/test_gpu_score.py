@@ -20,11 +20,12 @@ def reference(shape, tensors, toks):
 
 
 # Widths that end inside a group of 64 columns, with and without 16-byte rows; one
-# and two rows, which have heads of their own, also behind a launch of 1,024;
-# rows at the edges of the 16-row blocks, the tiles and the launches.
+# row (fp32: up to seven of these widths), which have heads of their own, also
+# behind a launch of 1,024; rows at the edges of the 16-row blocks, the tiles and
+# the launches.
 @pytest.mark.parametrize("dtype", [synth.BF16, synth.F32])
-@pytest.mark.parametrize("vocab,n", [(1000, 1), (1003, 2), (1003, 3), (1003, 15), (1000, 16), (1003, 17), (700, 64),
-                                     (700, 65), (530, 130), (257, 1025), (257, 1026), (257, 1030)])
+@pytest.mark.parametrize("vocab,n", [(1000, 1), (1003, 2), (1003, 3), (1003, 7), (1003, 8), (1003, 15), (1000, 16), (1003, 17), (700, 64),
+                                     (700, 65), (530, 130), (257, 1025), (257, 1026), (257, 1033)])
 def test_head_alone(dtype, vocab, n):
     import torch
     shape = synth.ModelShape(0, 512, 4, 2, 64, 64, vocab, 1e-5, 1e4, True, dtype)
