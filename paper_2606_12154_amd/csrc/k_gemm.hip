@@ -780,11 +780,11 @@ __device__ __forceinline__ void buffer_lds16(__amdgpu_buffer_rsrc_t r, lds_char*
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff, soff, 0, 0);
 }
 
-// Split products of one round whose units are dealt to the XCDs in turn, columns
-// first, so that an XCD works on every K split of a few column tiles: QKV (us at
-// 256 / 384 rows with the splits of tile_choice 14.6 / 15.3 in runs, 13.2 / 14.0
-// dealt; their partials take as long to write back as the K steps take).  The
-// down projection is no faster dealt (256 rows 17.9 / 18.0, 512 18.6 / 19.0).
+// Split products of one round whose units are dealt to the XCDs in turn, down the
+// rows first: QKV (us at 256 / 384 / 448 rows, with the splits of tile_choice, in
+// runs 14.6 / 15.3 / 16.5, dealt 12.4 / 13.7 / 15.6; along the columns first 13.3 /
+// 14.0 / 15.3).  Their partials take as long to write back as the K steps take.
+// The down projection is no faster dealt (256 rows 17.9 / 18.0, 512 18.6 / 19.0).
 template <class Epi>
 constexpr bool kDealSplits = false;
 template <typename TKV>
@@ -816,8 +816,8 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const _Float16* __restrict
     u.split = o / tiles;
     const int t = o - u.split * tiles;
     if (deal) {
-      u.n0 = (t % ntn) * BN;
-      u.m0 = (t / ntn) * BM;
+      u.n0 = (t / ntm) * BN;
+      u.m0 = (t % ntm) * BM;
     } else {
       constexpr int GM = 1024 / BM;
       const int band = t / (GM * ntn), r = t - band * GM * ntn, gm = min(GM, ntm - band * GM);
@@ -2095,8 +2095,8 @@ static TileCfg tile_choice(GemmKind kind, int M, int n_cols, int K) {
   // kernel): two or more row tiles of gate/up 26.9 / 33.6; the down
   // projection with K split over 256 workgroups 18.6 / 20.8; QKV from 256 rows
   // with the K splits, up to four, that fill one round (its reduction applies the
-  // epilogue): 256 rows, four, 13.2 + 6.3 / 12.8 + 7.0; 384 rows, three, 14.0 +
-  // 8.9 / 24.0 (four, two rounds, 17.7 + 8.2); 448 rows, two, 15.3 + 8.9 (four
+  // epilogue): 256 rows, four, 12.4 + 6.3 / 12.8 + 7.0; 384 rows, three, 13.7 +
+  // 8.9 / 24.0 (four, two rounds, 17.7 + 8.2); 448 rows, two, 15.6 + 8.9 (four
   // 18.0 + 9.0); O stays with the small tiles (13.4 / 8.7: few steps, and two
   // workgroups a CU hide each other's start).
   if (kind == GemmKind::GateUp && (n_cols < 8192 || M <= 128)) return TileCfg{0, 0, 1};
