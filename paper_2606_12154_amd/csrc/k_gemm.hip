@@ -729,22 +729,25 @@ __global__ __launch_bounds__(256) void k_splitk_finalize(const float* __restrict
 
 // ---------------------------------------------------------------- tile kernel (prompt prefill)
 
-// Prompt-sized GEMMs (M >= 128): BM x BN x 64 tiles, eight waves, each a block
-// of WM x 64 outputs as 16x16x32 MFMAs with the weights as the first operand:
-// a lane's four results are then four consecutive columns of one row, and with
-// the weight rows of a fragment taken in the order 8(r/4) + 4(j%2) + r%4 of
-// each 32, two fragments give it eight, so every store is 16 bytes.
+// Prompt-sized GEMMs (M >= 128, and the head of every row from two rows on, which
+// are 32 rows of fp16 terms): BM x BN x 64 tiles, eight waves, each a block of WM
+// x 64 outputs as 16x16x32 MFMAs with the weights as the first operand: a lane's
+// four results are then four consecutive columns of one row, and with the weight
+// rows of a fragment taken in the order 8(r/4) + 4(j%2) + r%4 of each 32, two
+// fragments give it eight, so every store is 16 bytes.
 //
-// What bounds it: with inputs of real spread the matrix cores run at the
-// card's power limit (8192 x 2048 x 8192: 138 us on zeros, 218 us on normal
-// draws, the same code), so what counts is the energy and the work beside the
-// MFMAs.  Against the kernel before (32x32x16 MFMAs, a workgroup per tile):
-// 16x16x32 forms move half the accumulator registers per product (gate/up at
-// 8192 rows 525 -> 505 us); one workgroup per CU walks the tiles of its XCD,
-// and its loads run on into the next tile (the load cursor below is NST steps
-// ahead of the MFMAs and knows nothing of tile ends), so neither the pipeline's
-// fill nor the epilogue's stores leave the matrix cores idle (505 -> 458 us,
-// 1,200 TFLOP/s).
+// What bounds it (counters, gate/up at 8192 rows, 256 x 256): the matrix cores are
+// busy for 55 % of the cycles.  A K step reads 192 KiB of fragments from the LDS
+// and writes 64 KiB into it, 2,048 cycles at 128 bytes each, as many as its MFMAs
+// take, and the two overlap in part.  On weights of real spread the clock is also
+// about 9 % lower than on zeros (448 against 410 us).  Against the kernel before
+// (32x32x16 MFMAs, a workgroup per tile): 16x16x32 forms move half the accumulator
+// registers per product (gate/up at 8192 rows 525 -> 505 us); one workgroup per CU
+// walks the tiles of its XCD, and its loads run on into the next tile (the load
+// cursor below is NST steps ahead of the MFMAs and knows nothing of tile ends), so
+// neither the pipeline's fill nor the epilogue's stores leave the matrix cores idle
+// (505 -> 448 us, 1,230 TFLOP/s; a library product of that shape without the
+// epilogue 500 us).
 //
 // K steps go global -> LDS with direct 16-byte loads through NST stages, the
 // addresses in scalar registers (a row group's offset and the step's) but
